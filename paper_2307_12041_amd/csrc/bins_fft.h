@@ -1,0 +1,34 @@
+// bins_fft.h -- fast cosine and sine transforms of the bin scheme (bins_fft.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace pp {
+
+// Transform length m (bins per axis) as complex transforms of length L, a power of two:
+//   m itself a power of two in [64, 8192]: L = m;
+//   any other m up to 4096: L the power of two from max(64, 2 m - 1) on (the convolution length of
+//   Bluestein's chirp transform).
+// Larger m (and 4096 < m < 16384 other than 8192) have L = 0: no complex transform of 8192 points
+// (144 KB of LDS) holds them, and the matrix products of bins.hip serve.
+struct BinFft {
+    int m, L;
+    bool chirp;          // L > m or m below 64: Bluestein's form
+    size_t table_bytes;  // device tables (twiddles, phases, chirp), filled by launch_bin_fft_tables
+};
+
+BinFft bin_fft_plan(int m);
+
+hipError_t launch_bin_fft_tables(const BinFft &f, double *tab, hipStream_t s);
+
+// Coefficients: Q[l][p] = sum_j P[l][j] C_p(j) (Q: m x Mp scratch), then
+// a[u][p] = disa(u, p) sum_l C_u(l) Q[l][p].
+hipError_t launch_bin_fft_coeffs(const BinFft &f, const double *tab, const double *P, double *Q, double *a, int Mu,
+                                 int Mp, double W, double H, hipStream_t s);
+
+// Field: R[u][j] = sum_p a_up C_p(j) and Rs[u][j] = sum_p (p pi / H) a_up S_p(j) (Mu x m scratch each), then psi, xi_x
+// and xi_y at the bin centres; a NULL output is not written.
+hipError_t launch_bin_fft_field(const BinFft &f, const double *tab, const double *a, double *R, double *Rs, double *psi,
+                                double *xix, double *xiy, int Mu, int Mp, double W, double H, hipStream_t s);
+
+}  // namespace pp
