@@ -6,7 +6,9 @@
 namespace pp {
 namespace {
 
-constexpr int kRedThreads = 256;
+constexpr int kRedThreads = 256;   // coefficients per block of the split-K reduction
+constexpr int kRedGroups = 4;      // threads per coefficient
+constexpr int kRedMaxBlocks = 1 << 20;   // a grid stays below 2^32 work-items
 
 // Deterministic block sum of one double per thread (butterfly inside waves, then wave order).
 __device__ __forceinline__ double block_sum(double v, double *scratch) {
@@ -26,41 +28,71 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 //   s_up = e_u e_p / (W H (w_u^2 + v_p^2)), e_0 = 1, e_k = 2, s_00 = 0
 // (the four coefficient cases of Sec. III-A written with one scale; a_00 = 0 is the
 // compatibility condition).  The energy partial of this block is sum a_up A_up.
-__global__ __launch_bounds__(kRedThreads) void k_reduce_scale(const void *__restrict__ part, int part_f32,
-                                                              int splits, int Mu, int Mp, double W, double H,
-                                                              double *__restrict__ a, double *__restrict__ epart) {
-    __shared__ double scratch[kRedThreads / 64];
+//
+// Bound by reading the partials.  A block takes 256 coefficients with kRedGroups threads each: thread group g sums
+// the splits g, g + kRedGroups, ..., eight loads in flight per thread, and the groups' sums add in LDS in group order.  (One
+// thread per coefficient with its loads in a chain reached 2.0 TB/s on 481 splits of 512 x 512 (249 us, now 130: 3.9 TB/s) and
+// was latency at 157 splits of 257 x 513 (45 us, now 20).)
+template <typename T>
+__global__ __launch_bounds__(kRedThreads * kRedGroups) void k_reduce_scale(const T *__restrict__ part, int splits, int Mu,
+                                                                           int Mp, double W, double H,
+                                                                           double *__restrict__ a,
+                                                                           double *__restrict__ epart, int nb) {
+    __shared__ double sums[kRedGroups][kRedThreads];
+    __shared__ double scratch[kRedThreads * kRedGroups / 64];
     const size_t MM = (size_t)Mu * (size_t)Mp;
-    const size_t idx = (size_t)blockIdx.x * kRedThreads + threadIdx.x;
-    double e = 0.0;
-    if (idx < MM) {
-        const int u = (int)(idx / (size_t)Mp), p = (int)(idx % (size_t)Mp);
+    const int t = threadIdx.x % kRedThreads, g = threadIdx.x / kRedThreads;
+    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
+        const size_t idx = (size_t)b * kRedThreads + t;
         double At = 0.0;
-        if (part_f32) {
-            const float *pf = (const float *)part;
-            for (int s = 0; s < splits; ++s) At += (double)pf[(size_t)s * MM + idx];
-        } else {
-            const double *pd = (const double *)part;
-            for (int s = 0; s < splits; ++s) At += pd[(size_t)s * MM + idx];
+        if (idx < MM) {
+            const T *__restrict__ p = part + idx;
+            int s = g;
+            for (; s + 7 * kRedGroups < splits; s += 8 * kRedGroups) {
+                T v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = p[(size_t)(s + k * kRedGroups) * MM];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) At += (double)v[k];
+            }
+            for (; s < splits; s += kRedGroups) At += (double)p[(size_t)s * MM];
         }
-        const double wu = (double)u * kPi / W, vp = (double)p * kPi / H;
-        const double wt = u ? wu : 1.0, vt = p ? vp : 1.0;
-        const double A = At / (wt * vt);
-        const double eps = (u ? 2.0 : 1.0) * (p ? 2.0 : 1.0);
-        const double sc = (u == 0 && p == 0) ? 0.0 : eps / (W * H * (wu * wu + vp * vp));
-        const double av = sc * A;
-        if (a) a[idx] = av;
-        e = av * A;
+        sums[g][t] = At;
+        __syncthreads();
+        double e = 0.0;
+        if (g == 0 && idx < MM) {
+#pragma unroll
+            for (int k = 1; k < kRedGroups; ++k) At += sums[k][t];
+            const int u = (int)(idx / (size_t)Mp), p = (int)(idx % (size_t)Mp);
+            const double wu = (double)u * kPi / W, vp = (double)p * kPi / H;
+            const double wt = u ? wu : 1.0, vt = p ? vp : 1.0;
+            const double A = At / (wt * vt);
+            const double eps = (u ? 2.0 : 1.0) * (p ? 2.0 : 1.0);
+            const double sc = (u == 0 && p == 0) ? 0.0 : eps / (W * H * (wu * wu + vp * vp));
+            const double av = sc * A;
+            if (a) a[idx] = av;
+            e = av * A;
+        }
+        const double sum = block_sum(e, scratch);
+        if (threadIdx.x == 0) epart[b] = sum;
+        __syncthreads();
     }
-    const double s = block_sum(e, scratch);
-    if (threadIdx.x == 0) epart[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(kRedThreads) void k_energy_final(const double *__restrict__ epart, int nb,
-                                                              double *__restrict__ E) {
-    __shared__ double scratch[kRedThreads / 64];
+constexpr int kEnergyThreads = 1024;
+
+__global__ __launch_bounds__(kEnergyThreads) void k_energy_final(const double *__restrict__ epart, int nb,
+                                                                 double *__restrict__ E) {
+    __shared__ double scratch[kEnergyThreads / 64];
     double v = 0.0;
-    for (int k = threadIdx.x; k < nb; k += kRedThreads) v += epart[k];
+    int k = threadIdx.x;
+    for (; k + 3 * kEnergyThreads < nb; k += 4 * kEnergyThreads) {
+        double x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = epart[k + r * kEnergyThreads];
+        v += (x[0] + x[1]) + (x[2] + x[3]);
+    }
+    for (; k < nb; k += kEnergyThreads) v += epart[k];
     const double s = block_sum(v, scratch);
     if (threadIdx.x == 0) *E = 0.5 * s;
 }
@@ -115,14 +147,19 @@ int reduce_scale_blocks(int Mu, int Mp) {
 hipError_t launch_reduce_scale(const void *part, bool part_f32, int splits, int Mu, int Mp, double W, double H,
                                double *a, double *epart, int *nblocks_out, hipStream_t s) {
     const int nb = reduce_scale_blocks(Mu, Mp);
-    hipLaunchKernelGGL(k_reduce_scale, dim3(nb), dim3(kRedThreads), 0, s, part, part_f32 ? 1 : 0, splits, Mu, Mp,
-                       W, H, a, epart);
+    const int grid = nb < kRedMaxBlocks ? nb : kRedMaxBlocks;
+    if (part_f32)
+        hipLaunchKernelGGL(k_reduce_scale<float>, dim3(grid), dim3(kRedThreads * kRedGroups), 0, s, (const float *)part,
+                           splits, Mu, Mp, W, H, a, epart, nb);
+    else
+        hipLaunchKernelGGL(k_reduce_scale<double>, dim3(grid), dim3(kRedThreads * kRedGroups), 0, s, (const double *)part,
+                           splits, Mu, Mp, W, H, a, epart, nb);
     if (nblocks_out) *nblocks_out = nb;
     return hipGetLastError();
 }
 
 hipError_t launch_energy_final(const double *epart, int nblocks, double *E, hipStream_t s) {
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kRedThreads), 0, s, epart, nblocks, E);
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kEnergyThreads), 0, s, epart, nblocks, E);
     return hipGetLastError();
 }
 
