@@ -357,15 +357,12 @@ struct BinLayout {
 
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
-// The matrix products need 8m doubles of tables; the fast transforms' tables (bins_fft.h) are larger where m is no power
-// of two.
-BinLayout bin_layout(const pp_bin_problem &B, bool fft) {
+BinLayout bin_layout(const pp_bin_problem &B) {
     BinLayout L{};
     const size_t m = (size_t)B.m;
     const size_t t1 = m * (size_t)B.Mp, t2 = 2 * (size_t)B.Mu * m;
-    const size_t tab = 8 * m * sizeof(double), ftab = fft ? bin_fft_plan(B.m).table_bytes : 0;
     L.tab = 0;
-    L.tmp = align256(tab > ftab ? tab : ftab);
+    L.tmp = align256(8 * m * sizeof(double));
     L.list = L.tmp + align256((t1 > t2 ? t1 : t2) * sizeof(double));
     L.total = L.list + align256(((size_t)(B.n > 0 ? B.n : 0) + 1) * sizeof(int));
     return L;
@@ -384,16 +381,10 @@ int check_bin_problem(const pp_bin_problem *B) {
 }
 
 int check_ws(const pp_bin_problem *B, void *ws, size_t ws_bytes) {
-    const BinLayout L = bin_layout(*B, false);
+    const BinLayout L = bin_layout(*B);
     if (ws_bytes < L.total) return PP_ERR_WORKSPACE;
     if (!ws || ((uintptr_t)ws & 255u)) return PP_ERR_ARG;
     return PP_OK;
-}
-
-// The transforms run as FFTs wherever a workgroup can hold one (bin_fft_plan), as matrix products elsewhere, and in a
-// workspace that holds the products' tables but not the FFT's.
-bool use_fft(const pp_bin_problem &B, size_t ws_bytes) {
-    return bin_fft_plan(B.m).L > 0 && ws_bytes >= bin_layout(B, true).total;
 }
 
 hipError_t fill_trig(int m, double *tab, hipStream_t s) {
@@ -412,7 +403,7 @@ int pp_bin_workspace_size(const pp_bin_problem *B, size_t *bytes) {
     int st = check_bin_problem(B);
     if (st != PP_OK) return st;
     if (!bytes) return PP_ERR_ARG;
-    *bytes = bin_layout(*B, true).total;
+    *bytes = bin_layout(*B).total;
     return PP_OK;
 }
 
@@ -424,7 +415,7 @@ int pp_bin_density(const pp_bin_problem *B, const double *x, const double *y, co
     if (B->n > 0 && (!x || !y || !w || !h || !al8(x) || !al8(y) || !al8(w) || !al8(h))) return PP_ERR_ARG;
     if ((st = check_ws(B, ws, ws_bytes)) != PP_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const BinLayout L = bin_layout(*B, false);
+    const BinLayout L = bin_layout(*B);
     int *list = (int *)((char *)ws + L.list);
     const size_t mm = (size_t)B->m * (size_t)B->m;
     BinGeom g{B->W, B->H, B->W / B->m, B->H / B->m, 1.0 / ((B->W / B->m) * (B->H / B->m)), B->m};
@@ -448,13 +439,12 @@ int pp_bin_coeffs(const pp_bin_problem *B, const double *P, double *a, void *ws,
     if (!P || !a || !al8(P) || !al8(a)) return PP_ERR_ARG;
     if ((st = check_ws(B, ws, ws_bytes)) != PP_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const bool fft = use_fft(*B, ws_bytes);
-    const BinLayout L = bin_layout(*B, fft);
+    const BinLayout L = bin_layout(*B);
     double *tab = (double *)((char *)ws + L.tab), *Q = (double *)((char *)ws + L.tmp);
     const int m = B->m;
     TimedLaunch t("bin_coeffs", s);
-    if (fft) {
-        const BinFft f = bin_fft_plan(m);
+    // as FFTs wherever a workgroup can hold one, as matrix products elsewhere
+    if (const BinFft f = bin_fft_plan(m); f.L > 0) {
         if (launch_bin_fft_tables(f, tab, s) != hipSuccess ||
             launch_bin_fft_coeffs(f, tab, P, Q, a, B->Mu, B->Mp, B->W, B->H, s) != hipSuccess)
             return PP_ERR_DEVICE;
@@ -479,15 +469,14 @@ int pp_bin_field(const pp_bin_problem *B, const double *a, double *psi, double *
     if ((st = check_ws(B, ws, ws_bytes)) != PP_OK) return st;
     if (!psi && !xix && !xiy) return PP_OK;
     hipStream_t s = (hipStream_t)stream;
-    const bool fft = use_fft(*B, ws_bytes);
-    const BinLayout L = bin_layout(*B, fft);
+    const BinLayout L = bin_layout(*B);
     const int m = B->m, Mu = B->Mu, Mp = B->Mp;
     double *tab = (double *)((char *)ws + L.tab);
     double *R = (double *)((char *)ws + L.tmp), *Rs = R + (size_t)Mu * m;
     const double wu = kPi / B->W, vp = kPi / B->H;
     TimedLaunch t("bin_field", s);
-    if (fft) {
-        const BinFft f = bin_fft_plan(m);
+    // as FFTs wherever a workgroup can hold one, as matrix products elsewhere
+    if (const BinFft f = bin_fft_plan(m); f.L > 0) {
         if (launch_bin_fft_tables(f, tab, s) != hipSuccess ||
             launch_bin_fft_field(f, tab, a, R, Rs, psi, xix, xiy, Mu, Mp, B->W, B->H, s) != hipSuccess)
             return PP_ERR_DEVICE;
@@ -523,7 +512,7 @@ int pp_bin_interp(const pp_bin_problem *B, const double *x, const double *y, con
     if ((st = check_ws(B, ws, ws_bytes)) != PP_OK) return st;
     if (!psi && !xix && !xiy) return PP_OK;
     hipStream_t s = (hipStream_t)stream;
-    const BinLayout L = bin_layout(*B, false);
+    const BinLayout L = bin_layout(*B);
     int *list = (int *)((char *)ws + L.list);
     BinGeom g{B->W, B->H, B->W / B->m, B->H / B->m, 1.0 / ((B->W / B->m) * (B->H / B->m)), B->m};
     InterpIO io{{psi, xix, xiy}, {N, gx, gy}};

@@ -7,18 +7,18 @@ namespace pp {
 
 // Transform length m (bins per axis) as complex transforms of length L, a power of two:
 //   m itself a power of two in [64, 8192]: L = m;
-//   any other m up to 4096: L the power of two from max(64, 2 m - 1) on (the convolution length of
+//   any other m up to 4096: L the power of two from max(8, 2 m - 1) on (the convolution length of
 //   Bluestein's chirp transform).
 // Larger m (and 4096 < m < 16384 other than 8192) have L = 0: no complex transform of 8192 points
 // (144 KB of LDS) holds them, and the matrix products of bins.hip serve.
 struct BinFft {
     int m, L;
-    bool chirp;          // L > m or m below 64: Bluestein's form
-    size_t table_bytes;  // device tables (twiddles, phases, chirp), filled by launch_bin_fft_tables
+    bool chirp;          // Bluestein's form
 };
 
 BinFft bin_fft_plan(int m);
 
+// Fills the device tables (8 m doubles: twiddles, phases, the chirp's transform) that the transforms read.
 hipError_t launch_bin_fft_tables(const BinFft &f, double *tab, hipStream_t s);
 
 // Coefficients: Q[l][p] = sum_j P[l][j] C_p(j) (Q: m x Mp scratch), then

@@ -35,19 +35,40 @@ __device__ __forceinline__ cplx cmul(cplx a, cplx b) { return cplx{a.x * b.x - a
 __device__ __forceinline__ cplx swapped(cplx a) { return cplx{a.y, a.x}; }
 __device__ __forceinline__ cplx times_minus_i(cplx a) { return cplx{a.y, -a.x}; }
 
-// Device tables: T[k] = (cos, sin)(pi k / 2N), k < N; W[k] = e^{-2 pi i k / L}, k < L; in Bluestein's form also
-// Ch[n] = e^{-i pi n^2 / N}, n < N, and Bh = DFT_L(b) / L.
+// Device tables, 8 N doubles at most (L < 4 N - 2):
+//   T[k] = e^{i pi k / 2N}, k < N;
+//   W[k] = e^{-2 pi i k / L}: k < L where L = N, one quadrant (k < L / 4) in Bluestein's form, which also has
+//   Bh[k] = DFT_L(b) / L, k <= L / 2 (b is even, so Bh[L - k] = Bh[k]).
 struct Tables {
-    const cplx *T, *W, *Ch, *Bh;
+    const cplx *T, *W, *Bh;
 };
 
 Tables tables(const BinFft &f, const double *tab) {
     Tables t;
     t.T = (const cplx *)tab;
     t.W = t.T + f.m;
-    t.Ch = t.W + f.L;
-    t.Bh = t.Ch + f.m;
+    t.Bh = t.W + f.L / 4;
     return t;
+}
+
+// z times i^q (q modulo 4).
+__device__ __forceinline__ cplx times_i_power(cplx z, int q) {
+    const cplx t = (q & 1) ? cplx{-z.y, z.x} : z;
+    return (q & 2) ? cplx{-t.x, -t.y} : t;
+}
+
+// e^{-2 pi i k / 2^lg} for 0 <= k < 2^lg.
+template <bool CHIRP>
+__device__ __forceinline__ cplx twiddle(const cplx *__restrict__ W, int k, int lg) {
+    if constexpr (!CHIRP) return W[k];
+    else return times_i_power(W[k & ((1 << (lg - 2)) - 1)], -(k >> (lg - 2)));
+}
+
+// b*_n = e^{-i pi n^2 / N}: the point 2 n^2 mod 4N of the circle that T holds a quadrant of (n^2 is exact in 32 bits).
+__device__ __forceinline__ cplx chirp_conj(const cplx *__restrict__ T, int n, int N) {
+    const int q = 2 * (int)(((unsigned)n * (unsigned)n) % (2u * (unsigned)N)), quad = q / N;
+    const cplx z = times_i_power(T[q - quad * N], quad);
+    return cplx{z.x, -z.y};
 }
 
 // LDS: one complex of padding after every eight, so that the 16 lanes of a b128 access phase fall on different banks in
@@ -74,10 +95,11 @@ __device__ __forceinline__ void fft8(cplx (&v)[8]) {
     for (int r = 0; r < 4; ++r) { v[2 * r] = s[r]; v[2 * r + 1] = d[r]; }
 }
 
-// In-place Stockham DFTs of length L = 2^lg (lg >= 6) of all transforms of the workgroup: the thread with index j of its
+// In-place Stockham DFTs of length L = 2^lg (lg >= 3) of all transforms of the workgroup: the thread with index j of its
 // transform's L / 8 threads holds eight points per stage.  x: the transform's base in LDS (padded); W: twiddles in global
 // memory (they stay in the caches).  Radix 8, after one radix 2 or 4 stage where 3 does not divide lg.  Every stage reads
 // its points, meets at a barrier and writes them; the caller's data has to be complete, and the result is when it returns.
+template <bool CHIRP>
 __device__ __forceinline__ void dft(cplx *x, int j, int lg, const cplx *__restrict__ W) {
     const int E = 1 << (lg - 3);
     const int rem = lg % 3;
@@ -115,7 +137,7 @@ __device__ __forceinline__ void dft(cplx *x, int j, int lg, const cplx *__restri
         if (ns > 1) {
             const int step = jm << sh;
 #pragma unroll
-            for (int r = 1; r < 8; ++r) v[r] = cmul(v[r], W[r * step]);
+            for (int r = 1; r < 8; ++r) v[r] = cmul(v[r], twiddle<CHIRP>(W, r * step, lg));
         }
         fft8(v);
         const int o = ((j - jm) << 3) + jm;
@@ -125,44 +147,41 @@ __device__ __forceinline__ void dft(cplx *x, int j, int lg, const cplx *__restri
     }
 }
 
-// All blocks: T and W.  Bluestein's form needs W and Ch before Bh and runs as one workgroup of L / 8 threads.
-__global__ void k_fft_tables(int N, int L, cplx *__restrict__ T, cplx *__restrict__ W) {
+// T and W where L = N.
+__global__ void k_fft_tables(int N, cplx *__restrict__ T, cplx *__restrict__ W) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= N) return;
     double s, c;
-    if (k < N) {
-        sincospi((double)k / (2.0 * N), &s, &c);
-        T[k] = cplx{c, s};
-    }
-    if (k < L) {
-        sincospi(2.0 * (double)k / (double)L, &s, &c);
-        W[k] = cplx{c, -s};
-    }
+    sincospi((double)k / (2.0 * N), &s, &c);
+    T[k] = cplx{c, s};
+    sincospi(2.0 * (double)k / (double)N, &s, &c);
+    W[k] = cplx{c, -s};
 }
 
-__global__ __launch_bounds__(1024) void k_fft_tables_chirp(int N, int lg, cplx *__restrict__ T, cplx *W, cplx *Ch,
-                                                           cplx *__restrict__ Bh) {
+// Bluestein's tables: one workgroup of L / 8 threads (Bh needs the others).
+__global__ __launch_bounds__(1024) void k_fft_tables_chirp(int N, int lg, cplx *T, cplx *W, cplx *__restrict__ Bh) {
     __shared__ cplx lds[lds_len(8192)];
     const int L = 1 << lg, tid = threadIdx.x, nt = blockDim.x;
     double s, c;
-    for (int k = tid; k < L; k += nt) {
+    for (int k = tid; k < L / 4; k += nt) {
         sincospi(2.0 * (double)k / (double)L, &s, &c);
         W[k] = cplx{c, -s};
-        lds[lpos(k)] = cplx{0.0, 0.0};
     }
-    __syncthreads();
+    for (int k = tid; k < L; k += nt) lds[lpos(k)] = cplx{0.0, 0.0};
     for (int k = tid; k < N; k += nt) {
         sincospi((double)k / (2.0 * N), &s, &c);
         T[k] = cplx{c, s};
-        // n^2 mod 2N is exact in 32 bits (N <= 4096)
-        sincospi((double)(((unsigned)k * (unsigned)k) % (2u * (unsigned)N)) / (double)N, &s, &c);
-        Ch[k] = cplx{c, -s};
-        lds[lpos(k)] = cplx{c, s};
-        if (k) lds[lpos(L - k)] = cplx{c, s};
     }
     __syncthreads();
-    dft(lds, tid, lg, W);
+    for (int k = tid; k < N; k += nt) {
+        const cplx b = chirp_conj(T, k, N);
+        lds[lpos(k)] = cplx{b.x, -b.y};
+        if (k) lds[lpos(L - k)] = cplx{b.x, -b.y};
+    }
+    __syncthreads();
+    dft<true>(lds, tid, lg, W);
     const double inv = 1.0 / (double)L;
-    for (int k = tid; k < L; k += nt) {
+    for (int k = tid; k <= L / 2; k += nt) {
         const cplx v = lds[lpos(k)];
         Bh[k] = cplx{v.x * inv, v.y * inv};
     }
@@ -218,7 +237,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
     const int ldi = PASS == ROW_FWD ? N : PASS == COL_FWD || PASS == ROW_INV ? A.Mp : N;
     const int ldo = PASS == ROW_FWD || PASS == COL_FWD ? A.Mp : N;
     cplx *x = lds + f * lds_len(L);
-    const cplx *__restrict__ T = A.t.T, *__restrict__ Ch = A.t.Ch;
+    const cplx *__restrict__ T = A.t.T;
 
     // ---- load: eight elements per thread at most, all in flight together ----
     cplx v[8];
@@ -238,7 +257,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
             if (n < N) {
                 const int pos = (n & 1) ? N - 1 - (n >> 1) : n >> 1;
                 cplx z = cplx{ok0 ? v[r].x : 0.0, ok1 ? v[r].y : 0.0};
-                if (CHIRP) z = cmul(z, Ch[pos]);
+                if (CHIRP) z = cmul(z, chirp_conj(T, pos, N));
                 x[lpos(pos)] = z;
             } else {
                 x[lpos(n)] = cplx{0.0, 0.0};   // Bluestein's zero padding, N .. L - 1
@@ -273,7 +292,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
                 z = cmul(z, T[k]);
                 if (k == 0) z = cplx{c[r].x, d[r].x};
                 z = swapped(z);
-                if (CHIRP) z = cmul(z, Ch[k]);
+                if (CHIRP) z = cmul(z, chirp_conj(T, k, N));
                 v[r] = z;
             } else {
                 v[r] = cplx{0.0, 0.0};
@@ -284,19 +303,19 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
     __syncthreads();
 
     // ---- transform ----
-    dft(x, j, lg, A.t.W);
+    dft<CHIRP>(x, j, lg, A.t.W);
     if constexpr (CHIRP) {
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const int k = j + r * E;
-            x[lpos(k)] = swapped(cmul(x[lpos(k)], A.t.Bh[k]));
+            x[lpos(k)] = swapped(cmul(x[lpos(k)], A.t.Bh[min(k, L - k)]));
         }
         __syncthreads();
-        dft(x, j, lg, A.t.W);
+        dft<true>(x, j, lg, A.t.W);
     }
     auto get = [&](int k) {
         const cplx z = x[lpos(k)];
-        return CHIRP ? cmul(swapped(z), Ch[k]) : z;
+        return CHIRP ? cmul(swapped(z), chirp_conj(T, k, N)) : z;
     };
 
     // ---- store ----
@@ -365,17 +384,14 @@ hipError_t launch_points(const BinFft &f, FftArgs A, int count, int jobs, hipStr
 }  // namespace
 
 BinFft bin_fft_plan(int m) {
-    BinFft f{m, 0, false, 0};
+    BinFft f{m, 0, false};
     if (m >= 64 && m <= 8192 && (m & (m - 1)) == 0) {
         f.L = m;
     } else if (m <= 4096) {
         f.chirp = true;
-        f.L = 64;
+        f.L = 8;
         while (f.L < 2 * m - 1) f.L *= 2;
-    } else {
-        return f;
     }
-    f.table_bytes = (size_t)(f.chirp ? 2 : 1) * (size_t)(f.m + f.L) * sizeof(cplx);
     return f;
 }
 
@@ -383,9 +399,9 @@ hipError_t launch_bin_fft_tables(const BinFft &f, double *tab, hipStream_t s) {
     const Tables t = tables(f, tab);
     if (f.chirp)
         hipLaunchKernelGGL(k_fft_tables_chirp, dim3(1), dim3(f.L / 8), 0, s, f.m,
-                           log2i(f.L), (cplx *)t.T, (cplx *)t.W, (cplx *)t.Ch, (cplx *)t.Bh);
+                           log2i(f.L), (cplx *)t.T, (cplx *)t.W, (cplx *)t.Bh);
     else
-        hipLaunchKernelGGL(k_fft_tables, dim3((unsigned)((f.L + 255) / 256)), dim3(256), 0, s, f.m, f.L, (cplx *)t.T,
+        hipLaunchKernelGGL(k_fft_tables, dim3((unsigned)((f.m + 255) / 256)), dim3(256), 0, s, f.m, (cplx *)t.T,
                            (cplx *)t.W);
     return hipGetLastError();
 }
