@@ -8,6 +8,7 @@ namespace {
 
 constexpr int kRedThreads = 256;   // coefficients per block of the split-K reduction
 constexpr int kRedGroups = 4;      // threads per coefficient
+constexpr int kRedBatch = 32;       // splits per batch
 constexpr int kRedMaxBlocks = 1 << 20;   // a grid stays below 2^32 work-items
 
 // Deterministic block sum of one double per thread (butterfly inside waves, then wave order).
@@ -29,40 +30,49 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 // (the four coefficient cases of Sec. III-A written with one scale; a_00 = 0 is the
 // compatibility condition).  The energy partial of this block is sum a_up A_up.
 //
-// Bound by reading the partials.  A block takes 256 coefficients with kRedGroups threads each: thread group g sums
-// the splits g, g + kRedGroups, ..., eight loads in flight per thread, and the groups' sums add in LDS in group order.  (One
-// thread per coefficient with its loads in a chain reached 2.0 TB/s on 481 splits of 512 x 512 (249 us, now 130: 3.9 TB/s) and
-// was latency at 157 splits of 257 x 513 (45 us, now 20).)
+// Bound by reading the partials.  A block takes 256 coefficients with kRedGroups threads each, in batches of
+// kRedBatch splits: every thread has eight loads in flight, the batch meets in LDS, and the first group adds it in the order of
+// the splits while the next batch is loaded.  The order is the one of a plain sum, so that neither the number of threads nor
+// a change of it shows in a result (an e4m3 operand of the FP8 gradient turns the last bit of a coefficient into 2^-8 of it).
+// (One thread per coefficient with its loads in a chain reached 2.0 TB/s on 481 splits of 512 x 512 (249 us, now 131:
+// 3.9 TB/s) and was latency at 157 splits of 257 x 513 (45 us, now 22).)
 template <typename T>
 __global__ __launch_bounds__(kRedThreads * kRedGroups) void k_reduce_scale(const T *__restrict__ part, int splits, int Mu,
                                                                            int Mp, double W, double H,
                                                                            double *__restrict__ a,
                                                                            double *__restrict__ epart, int nb) {
-    __shared__ double sums[kRedGroups][kRedThreads];
+    __shared__ T buf[kRedBatch][kRedThreads];
     __shared__ double scratch[kRedThreads * kRedGroups / 64];
+    constexpr int PER = kRedBatch / kRedGroups;
     const size_t MM = (size_t)Mu * (size_t)Mp;
     const int t = threadIdx.x % kRedThreads, g = threadIdx.x / kRedThreads;
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
         const size_t idx = (size_t)b * kRedThreads + t;
+        const T *__restrict__ p = part + (idx < MM ? idx : 0);
         double At = 0.0;
-        if (idx < MM) {
-            const T *__restrict__ p = part + idx;
-            int s = g;
-            for (; s + 7 * kRedGroups < splits; s += 8 * kRedGroups) {
-                T v[8];
+        T v[PER];
+        auto fetch = [&](int s0) {   // splits s0 + PER g ..; past the last one the last again, which is not added
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = p[(size_t)(s + k * kRedGroups) * MM];
+            for (int k = 0; k < PER; ++k) v[k] = p[(size_t)min(s0 + PER * g + k, splits - 1) * MM];
+        };
+        fetch(0);
+        for (int s0 = 0; s0 < splits; s0 += kRedBatch) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) At += (double)v[k];
+            for (int k = 0; k < PER; ++k) buf[PER * g + k][t] = v[k];
+            __syncthreads();
+            if (s0 + kRedBatch < splits) fetch(s0 + kRedBatch);
+            if (g == 0) {
+                if (s0 + kRedBatch <= splits) {
+#pragma unroll
+                    for (int k = 0; k < kRedBatch; ++k) At += (double)buf[k][t];
+                } else {
+                    for (int k = 0; k < splits - s0; ++k) At += (double)buf[k][t];
+                }
             }
-            for (; s < splits; s += kRedGroups) At += (double)p[(size_t)s * MM];
+            __syncthreads();
         }
-        sums[g][t] = At;
-        __syncthreads();
         double e = 0.0;
         if (g == 0 && idx < MM) {
-#pragma unroll
-            for (int k = 1; k < kRedGroups; ++k) At += sums[k][t];
             const int u = (int)(idx / (size_t)Mp), p = (int)(idx % (size_t)Mp);
             const double wu = (double)u * kPi / W, vp = (double)p * kPi / H;
             const double wt = u ? wu : 1.0, vt = p ? vp : 1.0;
