@@ -255,10 +255,10 @@ const char *pp_strerror(int status);
  * kernel launch it enqueues, on the caller's stream; pp_timing_enable(0) stops recording.  Either
  * call first discards all earlier records and their events.
  * pp_timing_query(name, &ms, &count) waits for the recorded events of one stage and returns their
- * summed duration in milliseconds and the number of launches.  Stage names: "tables" (per-block
- * phase records), "seeds" (run seeds of the bf16 forward), "fwd" (coefficient contraction), "reduce" (split-K sum, scale, energy
- * partials), "energy" (final energy sum), "prep" (row-form operands), "bwd" (the two gradient
- * contractions, one record each), "final" (per-block partial sums), "build" (store-mode basis
+ * summed duration in milliseconds and the number of records.  Stage names: "tables" (per-block
+ * phase records, and the run seeds of a forward), "fwd" (coefficient contraction), "reduce" (split-K sum, scale, energy
+ * partials), "energy" (final energy sum), "prep" (row-form operands; bf16 types: and the phase records), "bwd" (the two
+ * gradient contractions, one record for both), "final" (per-block partial sums), "build" (store-mode basis
  * tables), "point" (pp_point_field
  * contractions), "potential" (pp_block_potential contraction), "bin_density", "bin_coeffs",
  * "bin_field", "bin_interp" (the bin scheme, all launches of one call in one record).  Unknown names give count 0.

@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <initializer_list>
 #include <mutex>
 
 #include "../../include/pplace.h"
@@ -260,12 +261,10 @@ int run_forward(const pp_problem &P, const double *x, const double *y, const dou
         const bool x3 = P.precision == PP_BF16X3 || P.precision == PP_FP8X3;
         PhaseRec *tx = (PhaseRec *)(base + L.tx), *ty = (PhaseRec *)(base + L.ty);
         RunSeed *sx = (RunSeed *)(base + L.sdx), *sy = (RunSeed *)(base + L.sdy);
-        { TimedLaunch t(T("tables"), s); err = launch_phase_tables(P.n, x, y, w, h, P.W, P.H, tx, ty, s); }
-        if (err != hipSuccess) return PP_ERR_DEVICE;
         {
-            TimedLaunch t(T("seeds"), s);
-            err = launch_seed_table(P.n, seed_runs(P.Mu), tx, sx, s);
-            if (err == hipSuccess) err = launch_seed_table(P.n, seed_runs(P.Mp), ty, sy, s);
+            TimedLaunch t(T("tables"), s);
+            err = launch_axis_tables(P.n, AxisTables{x, w, P.W, tx, sx, seed_runs(P.Mu)},
+                                     AxisTables{y, h, P.H, ty, sy, seed_runs(P.Mp)}, s);
         }
         if (err != hipSuccess) return PP_ERR_DEVICE;
         if (P.basis_mode == PP_BASIS_STORE) {
@@ -334,8 +333,37 @@ hipError_t prep_rowform(const pp_problem &P, RowForm f, const double *a, void *b
     return launch_prep_rowform_f64(f, a, P.Mu, P.Mp, P.W, P.H, (double *)bx, (double *)by, s);
 }
 
-hipError_t rowform(const pp_problem &P, RowForm f, const BwdPlan &b, const BwdAxis &ax, hipStream_t s) {
-    return P.precision == PP_FP32 ? launch_rowform_f32(f, b, P.n, ax, s) : launch_rowform_f64(f, b, P.n, ax, s);
+hipError_t rowform(const pp_problem &P, RowForm f, const BwdPlan &b, const BwdAxis &ax0, const BwdAxis *ax1,
+                   hipStream_t s) {
+    return P.precision == PP_FP32 ? launch_rowform_f32(f, b, P.n, ax0, ax1, s)
+                                  : launch_rowform_f64(f, b, P.n, ax0, ax1, s);
+}
+
+// Whether the contractions may write results themselves (RowOut) while others of them still read their inputs: the FP64 and
+// FP32 kernels read the block arrays, so no output may share memory with one; the other types read tables made before.
+bool outputs_apart(const pp_problem &P, std::initializer_list<const double *> outs,
+                   std::initializer_list<const double *> ins) {
+    if (is_gen(P.precision)) return true;
+    const uintptr_t bytes = (uintptr_t)P.n * sizeof(double);
+    for (const double *o : outs)
+        for (const double *i : ins)
+            if (o && i && (uintptr_t)o < (uintptr_t)i + bytes && (uintptr_t)i < (uintptr_t)o + bytes) return false;
+    return true;
+}
+
+// Where a contraction's row sums end: an N axis of one tile writes the results itself where it may (`direct`), and
+// k_bwd_final adds the partial sums of the others.
+RowOut row_out(bool direct, int tiles_n, double *r, double *r2, const double *dE) {
+    return direct && tiles_n == 1 ? RowOut{r, r2, dE} : RowOut{nullptr, nullptr, nullptr};
+}
+
+hipError_t sum_partials(bool direct, const double *gpx, int tx, double *gx, const double *gpy, int ty, double *gy,
+                        int64_t n, const double *dE, hipStream_t s) {
+    if (direct && tx == 1) gx = nullptr;
+    if (direct && ty == 1) gy = nullptr;
+    if (!gx && !gy) return hipSuccess;
+    TimedLaunch t("final", s);
+    return launch_bwd_final(gpx, tx, gpy, ty, n, dE, gx, gy, s);
 }
 
 }  // namespace
@@ -406,49 +434,51 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
     const BwdPlan b = bwd_plan(*P);
     char *base = (char *)ws;
     double *gpx = (double *)(base + L.gpx), *gpy = (double *)(base + L.gpy);
+    // the FP8 types and the stored basis have partial sums for every N axis
+    const bool direct = !is_fp8(P->precision) && P->basis_mode == PP_BASIS_RECOMPUTE && outputs_apart(*P, {gx, gy}, {x, y, w, h});
+    const RowOut ox = row_out(direct, b.tiles_nx, gx, nullptr, dE), oy = row_out(direct, b.tiles_ny, gy, nullptr, dE);
     if (is_fp8(P->precision)) {
         const bool x3 = P->precision == PP_FP8X3;
         PhaseRec *tx = (PhaseRec *)(base + L.tx), *ty = (PhaseRec *)(base + L.ty);
         unsigned char *bxt = (unsigned char *)(base + L.bx), *byt = (unsigned char *)(base + L.by);
         float *b0x = (float *)(base + L.b0x), *b0y = (float *)(base + L.b0y);
         const int khx = bf16_kh(P->Mp), khy = bf16_kh(P->Mu);
-        { TimedLaunch t("tables", s); if (launch_phase_tables(P->n, x, y, w, h, P->W, P->H, tx, ty, s) != hipSuccess) return PP_ERR_DEVICE; }
+        {
+            TimedLaunch t("tables", s);
+            if (launch_axis_tables(P->n, AxisTables{x, w, P->W, tx, nullptr, 0}, AxisTables{y, h, P->H, ty, nullptr, 0},
+                                   s) != hipSuccess)
+                return PP_ERR_DEVICE;
+        }
         {
             TimedLaunch t("prep", s);
-            if (launch_prep_bwd_fp8(ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H, 0, b.tiles_nx * 256, khx, bxt, b0x, s) !=
-                hipSuccess)
-                return PP_ERR_DEVICE;
-            if (launch_prep_bwd_fp8(ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H, 1, b.tiles_ny * 256, khy, byt, b0y, s) !=
+            if (launch_prep_bwd_fp8(ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H,
+                                    {{b.tiles_nx * 256, khx, bxt, b0x}, {b.tiles_ny * 256, khy, byt, b0y}}, s) !=
                 hipSuccess)
                 return PP_ERR_DEVICE;
         }
         // gx: K = p (basis of y), epilogue over u (x);  gy: K = u (basis of x), epilogue over p (y).
         const BwdAxisFp8 axx{ty, tx, P->Mp, P->Mu, khx, bxt, b0x, gpx, nullptr, 0.0f};
         const BwdAxisFp8 axy{tx, ty, P->Mu, P->Mp, khy, byt, b0y, gpy, nullptr, 0.0f};
-        { TimedLaunch t("bwd", s); if (launch_bwd_fp8(ROW_FIELD, x3, P->n, axx, s) != hipSuccess) return PP_ERR_DEVICE; }
-        { TimedLaunch t("bwd", s); if (launch_bwd_fp8(ROW_FIELD, x3, P->n, axy, s) != hipSuccess) return PP_ERR_DEVICE; }
-        { TimedLaunch t("final", s); if (launch_bwd_final(gpx, b.tiles_nx, gpy, b.tiles_ny, P->n, dE, gx, gy, s) != hipSuccess) return PP_ERR_DEVICE; }
-        return PP_OK;
-    }
-    if (is_bf16(P->precision)) {
-        const bool x3 = P->precision == PP_BF16X3;
+        TimedLaunch t("bwd", s);
+        if (launch_bwd_fp8(ROW_FIELD, x3, P->n, axx, s) != hipSuccess ||
+            launch_bwd_fp8(ROW_FIELD, x3, P->n, axy, s) != hipSuccess)
+            return PP_ERR_DEVICE;
+    } else if (is_bf16(P->precision)) {
+        const bool x3 = P->precision == PP_BF16X3, store = P->basis_mode == PP_BASIS_STORE;
         PhaseRec *tx = (PhaseRec *)(base + L.tx), *ty = (PhaseRec *)(base + L.ty);
         unsigned short *bxt = (unsigned short *)(base + L.bx), *byt = (unsigned short *)(base + L.by);
         const int khx = bf16_kh(P->Mp), khy = bf16_kh(P->Mu);
-        { TimedLaunch t("tables", s); if (launch_phase_tables(P->n, x, y, w, h, P->W, P->H, tx, ty, s) != hipSuccess) return PP_ERR_DEVICE; }
         {
             TimedLaunch t("prep", s);
-            if (launch_prep_bwd_bf16(ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H, 0, b.tiles_nx * 256, khx, bxt, s) !=
-                hipSuccess)
-                return PP_ERR_DEVICE;
-            if (launch_prep_bwd_bf16(ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H, 1, b.tiles_ny * 256, khy, byt, s) !=
-                hipSuccess)
+            if (launch_setup_bf16(P->n, AxisTables{x, w, P->W, tx, nullptr, 0}, AxisTables{y, h, P->H, ty, nullptr, 0},
+                                  ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H,
+                                  {{b.tiles_nx * 256, khx, bxt}, {b.tiles_ny * 256, khy, byt}}, s) != hipSuccess)
                 return PP_ERR_DEVICE;
         }
         // gx: K = p (basis of y), epilogue over u (x);  gy: K = u (basis of x), epilogue over p (y).
-        BwdAxisBf16 axx{ty, tx, P->Mp, P->Mu, khx, bxt, gpx, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f};
-        BwdAxisBf16 axy{tx, ty, P->Mu, P->Mp, khy, byt, gpy, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f};
-        if (P->basis_mode == PP_BASIS_STORE) {
+        BwdAxisBf16 axx{ty, tx, P->Mp, P->Mu, khx, bxt, gpx, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f, 0, 0, ox};
+        BwdAxisBf16 axy{tx, ty, P->Mu, P->Mp, khy, byt, gpy, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f, 0, 0, oy};
+        if (store) {
             // the tables that pp_coeffs / pp_energy left in the workspace
             const StoreTables st = store_tables(*P, L, base);
             const int tb = (int)((P->n + 255) / 256);
@@ -457,38 +487,35 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
             axy.tab_h = st.xh; axy.tab_l = st.xl; axy.tab_ld = st.ldx;
             axy.tiles_b = tb; axy.tiles_n = (P->Mp + 255) / 256;
         }
+        TimedLaunch t("bwd", s);
         if (P->precision == PP_BF16MIX) {
             // the low-frequency N tiles with three products, the others with one (the K axis whole in
             // both); each launch writes the partial row sums of its own N tiles
             const int rx = mix_tiles(P->Mu), ry = mix_tiles(P->Mp);
-            for (int axis = 0; axis < 2; ++axis) {
-                TimedLaunch t("bwd", s);
-                BwdAxisBf16 lo = axis == 0 ? axx : axy, hi = lo;
-                const int r = axis == 0 ? rx : ry, tn = axis == 0 ? b.tiles_nx : b.tiles_ny;
-                lo.nt0 = 0; lo.nt_end = r;
-                if (launch_bwd_bf16(ROW_FIELD, true, P->n, lo, s) != hipSuccess) return PP_ERR_DEVICE;
-                if (r < tn) {
-                    hi.nt0 = r; hi.nt_end = tn;
-                    if (launch_bwd_bf16(ROW_FIELD, false, P->n, hi, s) != hipSuccess) return PP_ERR_DEVICE;
-                }
-            }
-        } else {
-            { TimedLaunch t("bwd", s); if (launch_bwd_bf16(ROW_FIELD, x3, P->n, axx, s) != hipSuccess) return PP_ERR_DEVICE; }
-            { TimedLaunch t("bwd", s); if (launch_bwd_bf16(ROW_FIELD, x3, P->n, axy, s) != hipSuccess) return PP_ERR_DEVICE; }
+            BwdAxisBf16 hx = axx, hy = axy;
+            axx.nt_end = hx.nt0 = rx;
+            axy.nt_end = hy.nt0 = ry;
+            hx.nt_end = b.tiles_nx;
+            hy.nt_end = b.tiles_ny;
+            if (launch_bwd_bf16(ROW_FIELD, true, P->n, axx, &axy, s) != hipSuccess) return PP_ERR_DEVICE;
+            const bool ux = rx < b.tiles_nx, uy = ry < b.tiles_ny;
+            if ((ux || uy) &&
+                launch_bwd_bf16(ROW_FIELD, false, P->n, ux ? hx : hy, ux && uy ? &hy : nullptr, s) != hipSuccess)
+                return PP_ERR_DEVICE;
+        } else if (launch_bwd_bf16(ROW_FIELD, x3, P->n, axx, &axy, s) != hipSuccess) {
+            return PP_ERR_DEVICE;
         }
-        { TimedLaunch t("final", s); if (launch_bwd_final(gpx, b.tiles_nx, gpy, b.tiles_ny, P->n, dE, gx, gy, s) != hipSuccess) return PP_ERR_DEVICE; }
-        return PP_OK;
+    } else {
+        void *bx = base + L.bx, *by = base + L.by;
+        if (prep_rowform(*P, ROW_FIELD, a, bx, by, s) != hipSuccess) return PP_ERR_DEVICE;
+        // gx: K = p (basis of y), epilogue over u (cosine differences of x), operand BxT[p][u].
+        BwdAxis axx{y, h, P->H, P->Mp, x, w, P->W, P->Mu, bx, gpx, nullptr, ox};
+        // gy: K = u (basis of x), epilogue over p (cosine differences of y), operand By[u][p].
+        BwdAxis axy{x, w, P->W, P->Mu, y, h, P->H, P->Mp, by, gpy, nullptr, oy};
+        TimedLaunch t("bwd", s);
+        if (rowform(*P, ROW_FIELD, b, axx, &axy, s) != hipSuccess) return PP_ERR_DEVICE;
     }
-    void *bx = base + L.bx, *by = base + L.by;
-    if (prep_rowform(*P, ROW_FIELD, a, bx, by, s) != hipSuccess) return PP_ERR_DEVICE;
-    // gx: K = p (basis of y), epilogue over u (cosine differences of x), operand BxT[p][u].
-    BwdAxis axx{y, h, P->H, P->Mp, x, w, P->W, P->Mu, bx, gpx, nullptr};
-    // gy: K = u (basis of x), epilogue over p (cosine differences of y), operand By[u][p].
-    BwdAxis axy{x, w, P->W, P->Mu, y, h, P->H, P->Mp, by, gpy, nullptr};
-    { TimedLaunch t("bwd", s); if (rowform(*P, ROW_FIELD, b, axx, s) != hipSuccess) return PP_ERR_DEVICE; }
-    { TimedLaunch t("bwd", s); if (rowform(*P, ROW_FIELD, b, axy, s) != hipSuccess) return PP_ERR_DEVICE; }
-    { TimedLaunch t("final", s); if (launch_bwd_final(gpx, b.tiles_nx, gpy, b.tiles_ny, P->n, dE, gx, gy, s) != hipSuccess) return PP_ERR_DEVICE; }
-    return PP_OK;
+    return sum_partials(direct, gpx, b.tiles_nx, gx, gpy, b.tiles_ny, gy, P->n, dE, s) == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
 int pp_point_field(const pp_problem *P, const double *px, const double *py, const double *a, double *psi,
@@ -508,62 +535,54 @@ int pp_point_field(const pp_problem *P, const double *px, const double *py, cons
     char *base = (char *)ws;
     double *gp1 = (double *)(base + L.gpx), *gp2 = (double *)(base + L.gpz), *gpy = (double *)(base + L.gpy);
     void *bx = base + L.bx, *by = base + L.by;
+    // psi and xi_x share Z_iu = sum_p a_up cos(v_p y_i) (K = p, operand a^T); epilogues over u with cos(w_u x_i) and
+    // w_u sin(w_u x_i).  xi_y: K = u with cos(w_u x_i), operand a[u][p], epilogue over p with v_p sin(v_p y_i).
+    const RowForm f = psi ? ROW_POINT_DUAL : ROW_POINT_WSIN;
+    const bool direct = outputs_apart(*P, {psi, xix, xiy}, {px, py});
+    const RowOut ox = row_out(direct, b.tiles_nx, psi ? psi : xix, psi ? xix : nullptr, nullptr);
+    const RowOut oy = row_out(direct, b.tiles_ny, xiy, nullptr, nullptr);
+    double *g1 = psi ? gp1 : gp2, *g2 = psi ? gp2 : nullptr;
     if (is_bf16(P->precision)) {
         // bf16 operands: point phase records (size 0), hi/lo tiled a, the bf16 row-form kernels.
         const bool x3 = P->precision == PP_BF16X3;
         PhaseRec *tx = (PhaseRec *)(base + L.tx), *ty = (PhaseRec *)(base + L.ty);
         unsigned short *bxt = (unsigned short *)bx, *byt = (unsigned short *)by;
         const int khx = bf16_kh(P->Mp), khy = bf16_kh(P->Mu);
-        { TimedLaunch t("tables", s); if (launch_phase_tables(P->n, px, py, nullptr, nullptr, P->W, P->H, tx, ty, s) != hipSuccess) return PP_ERR_DEVICE; }
         {
             TimedLaunch t("prep", s);
-            if ((psi || xix) &&
-                launch_prep_bwd_bf16(ROW_POINT_DUAL, a, P->Mu, P->Mp, P->W, P->H, 0, b.tiles_nx * 256, khx, bxt, s) !=
-                    hipSuccess)
-                return PP_ERR_DEVICE;
-            if (xiy &&
-                launch_prep_bwd_bf16(ROW_POINT_DUAL, a, P->Mu, P->Mp, P->W, P->H, 1, b.tiles_ny * 256, khy, byt, s) !=
-                    hipSuccess)
+            if (launch_setup_bf16(P->n, AxisTables{px, nullptr, P->W, tx, nullptr, 0},
+                                  AxisTables{py, nullptr, P->H, ty, nullptr, 0}, ROW_POINT_DUAL, a, P->Mu, P->Mp, P->W,
+                                  P->H, {{psi || xix ? b.tiles_nx * 256 : 0, khx, bxt}, {xiy ? b.tiles_ny * 256 : 0, khy, byt}},
+                                  s) != hipSuccess)
                 return PP_ERR_DEVICE;
         }
+        const BwdAxisBf16 axx{ty, tx, P->Mp, P->Mu, khx, bxt, g1, nullptr, nullptr, 0, 0, 0,
+                              g2, (float)(kPi / P->W), 0, 0, ox};
+        const BwdAxisBf16 axy{tx, ty, P->Mu, P->Mp, khy, byt, gpy, nullptr, nullptr, 0, 0, 0,
+                              nullptr, (float)(kPi / P->H), 0, 0, oy};
         if (psi || xix) {
             TimedLaunch t("point", s);
-            const RowForm f = psi ? ROW_POINT_DUAL : ROW_POINT_WSIN;
-            BwdAxisBf16 ax{ty, tx, P->Mp, P->Mu, khx, bxt, psi ? gp1 : gp2, nullptr, nullptr, 0, 0, 0,
-                           psi ? gp2 : nullptr, (float)(kPi / P->W)};
-            if (launch_bwd_bf16(f, x3, P->n, ax, s) != hipSuccess) return PP_ERR_DEVICE;
+            if (launch_bwd_bf16(f, x3, P->n, axx, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
         }
         if (xiy) {
             TimedLaunch t("point", s);
-            BwdAxisBf16 ax{tx, ty, P->Mu, P->Mp, khy, byt, gpy, nullptr, nullptr, 0, 0, 0, nullptr, (float)(kPi / P->H)};
-            if (launch_bwd_bf16(ROW_POINT_WSIN, x3, P->n, ax, s) != hipSuccess) return PP_ERR_DEVICE;
+            if (launch_bwd_bf16(ROW_POINT_WSIN, x3, P->n, axy, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
         }
-        TimedLaunch t("final", s);
-        if (launch_bwd_final(gp1, b.tiles_nx, gpy, b.tiles_ny, P->n, nullptr, psi, xiy, s) != hipSuccess)
-            return PP_ERR_DEVICE;
-        if (xix && launch_bwd_final(gp2, b.tiles_nx, gp2, 0, P->n, nullptr, xix, nullptr, s) != hipSuccess)
-            return PP_ERR_DEVICE;
-        return PP_OK;
+    } else {
+        if (prep_rowform(*P, ROW_POINT_DUAL, a, bx, xiy ? by : nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
+        const BwdAxis axx{py, nullptr, P->H, P->Mp, px, nullptr, P->W, P->Mu, bx, g1, g2, ox};
+        const BwdAxis axy{px, nullptr, P->W, P->Mu, py, nullptr, P->H, P->Mp, by, gpy, nullptr, oy};
+        if (psi || xix) {
+            TimedLaunch t("point", s);
+            if (rowform(*P, f, b, axx, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
+        }
+        if (xiy) {
+            TimedLaunch t("point", s);
+            if (rowform(*P, ROW_POINT_WSIN, b, axy, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
+        }
     }
-    if (prep_rowform(*P, ROW_POINT_DUAL, a, bx, xiy ? by : nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
-    // psi and xi_x share Z_iu = sum_p a_up cos(v_p y_i) (K = p, operand a^T); epilogues over u with
-    // cos(w_u x_i) and w_u sin(w_u x_i).
-    if (psi || xix) {
-        TimedLaunch t("point", s);
-        const RowForm f = psi ? ROW_POINT_DUAL : ROW_POINT_WSIN;
-        BwdAxis ax{py, nullptr, P->H, P->Mp, px, nullptr, P->W, P->Mu, bx, psi ? gp1 : gp2, psi ? gp2 : nullptr};
-        if (rowform(*P, f, b, ax, s) != hipSuccess) return PP_ERR_DEVICE;
-    }
-    // xi_y: K = u with cos(w_u x_i), operand a[u][p], epilogue over p with v_p sin(v_p y_i).
-    if (xiy) {
-        TimedLaunch t("point", s);
-        BwdAxis ax{px, nullptr, P->W, P->Mu, py, nullptr, P->H, P->Mp, by, gpy, nullptr};
-        if (rowform(*P, ROW_POINT_WSIN, b, ax, s) != hipSuccess) return PP_ERR_DEVICE;
-    }
-    TimedLaunch t("final", s);
-    if (launch_bwd_final(gp1, b.tiles_nx, gpy, b.tiles_ny, P->n, nullptr, psi, xiy, s) != hipSuccess)
-        return PP_ERR_DEVICE;
-    if (xix && launch_bwd_final(gp2, b.tiles_nx, gp2, 0, P->n, nullptr, xix, nullptr, s) != hipSuccess)
+    if (sum_partials(direct, gp1, b.tiles_nx, psi, gpy, b.tiles_ny, xiy, P->n, nullptr, s) != hipSuccess ||
+        sum_partials(direct, gp2, b.tiles_nx, xix, nullptr, 0, nullptr, P->n, nullptr, s) != hipSuccess)
         return PP_ERR_DEVICE;
     return PP_OK;
 }
@@ -585,37 +604,32 @@ int pp_block_potential(const pp_problem *P, const double *x, const double *y, co
     char *base = (char *)ws;
     double *gp = (double *)(base + L.gpx);
     void *bx = base + L.bx;
+    const bool direct = outputs_apart(*P, {N}, {x, y, w, h});
+    const RowOut o = row_out(direct, b.tiles_nx, N, nullptr, nullptr);
+    // N_i = sum_u S_iu sum_p T_ip a_up / (vt_p wt_u): K = p, epilogue over u, both sine differences.
     if (is_bf16(P->precision)) {
         const bool x3 = P->precision == PP_BF16X3;
         PhaseRec *tx = (PhaseRec *)(base + L.tx), *ty = (PhaseRec *)(base + L.ty);
         unsigned short *bxt = (unsigned short *)bx;
         const int khx = bf16_kh(P->Mp);
-        { TimedLaunch t("tables", s); if (launch_phase_tables(P->n, x, y, w, h, P->W, P->H, tx, ty, s) != hipSuccess) return PP_ERR_DEVICE; }
         {
             TimedLaunch t("prep", s);
-            if (launch_prep_bwd_bf16(ROW_POTENTIAL, a, P->Mu, P->Mp, P->W, P->H, 0, b.tiles_nx * 256, khx, bxt, s) !=
-                hipSuccess)
+            if (launch_setup_bf16(P->n, AxisTables{x, w, P->W, tx, nullptr, 0}, AxisTables{y, h, P->H, ty, nullptr, 0},
+                                  ROW_POTENTIAL, a, P->Mu, P->Mp, P->W, P->H,
+                                  {{b.tiles_nx * 256, khx, bxt}, {0, 32, nullptr}}, s) != hipSuccess)
                 return PP_ERR_DEVICE;
         }
-        {
-            TimedLaunch t("potential", s);
-            BwdAxisBf16 ax{ty, tx, P->Mp, P->Mu, khx, bxt, gp, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f};
-            if (launch_bwd_bf16(ROW_POTENTIAL, x3, P->n, ax, s) != hipSuccess) return PP_ERR_DEVICE;
-        }
-        TimedLaunch t("final", s);
-        if (launch_bwd_final(gp, b.tiles_nx, gp, 0, P->n, nullptr, N, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
-        return PP_OK;
-    }
-    if (prep_rowform(*P, ROW_POTENTIAL, a, bx, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
-    // N_i = sum_u S_iu sum_p T_ip a_up / (vt_p wt_u): K = p, epilogue over u, both sine differences.
-    {
+        const BwdAxisBf16 ax{ty, tx, P->Mp, P->Mu, khx, bxt, gp, nullptr, nullptr, 0, 0, 0, nullptr, 0.0f, 0, 0, o};
         TimedLaunch t("potential", s);
-        BwdAxis ax{y, h, P->H, P->Mp, x, w, P->W, P->Mu, bx, gp, nullptr};
-        if (rowform(*P, ROW_POTENTIAL, b, ax, s) != hipSuccess) return PP_ERR_DEVICE;
+        if (launch_bwd_bf16(ROW_POTENTIAL, x3, P->n, ax, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
+    } else {
+        if (prep_rowform(*P, ROW_POTENTIAL, a, bx, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
+        const BwdAxis ax{y, h, P->H, P->Mp, x, w, P->W, P->Mu, bx, gp, nullptr, o};
+        TimedLaunch t("potential", s);
+        if (rowform(*P, ROW_POTENTIAL, b, ax, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
     }
-    TimedLaunch t("final", s);
-    if (launch_bwd_final(gp, b.tiles_nx, gp, 0, P->n, nullptr, N, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
-    return PP_OK;
+    return sum_partials(direct, gp, b.tiles_nx, N, nullptr, 0, nullptr, P->n, nullptr, s) == hipSuccess ? PP_OK
+                                                                                                       : PP_ERR_DEVICE;
 }
 
 const char *pp_strerror(int status) {

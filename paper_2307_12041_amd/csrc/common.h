@@ -37,6 +37,26 @@ struct BwdPlan {
     size_t bmat_elem;    // bytes per element of the prepared backward operand matrices
 };
 
+// Final outputs of a row-form contraction whose N axis is one tile: its row sums are then whole, and it writes dE times them
+// (dE NULL: 1) to r (and r2, the second epilogue) instead of partial sums.  r NULL: partial sums.
+struct RowOut {
+    double *r, *r2;
+    const double *dE;
+};
+
+// The contractions of one launch: the second one's N tiles follow the first one's on grid axis y (tiles0 of them; a launch
+// of one contraction has no workgroup beyond).  Each alone fills the chip badly where its workgroups are few, and its last
+// wave of workgroups leaves CUs idle.
+template <typename A> struct AxisPair {
+    A a[2];
+    int tiles0;
+    __device__ __forceinline__ A pick(bool second) const {
+        A r = a[0];
+        if (second) r = a[1];
+        return r;
+    }
+};
+
 // Arguments of one backward contraction (gx or gy), see common.h header comment.
 struct BwdAxis {
     const double *ca, *sa;   // K-side basis: coordinates and sizes (y,h for gx; x,w for gy)
@@ -48,6 +68,7 @@ struct BwdAxis {
     const void *B;           // prepared operand [Ka][Nb] (layout depends on precision)
     double *gpart;           // out: [tiles_n][n] partial row sums (first epilogue)
     double *gpart2;          // out: [tiles_n][n] partial row sums of the second epilogue, if any
+    RowOut out;
 };
 
 // Kinds of per-block basis values along one axis (frequency k, w_k = k pi / L, block centre c,
@@ -129,6 +150,7 @@ struct BwdAxisBf16 {
     // Recompute mode: the launch covers N tiles nt0 .. nt_end - 1 (nt_end = 0: all N tiles), so that
     // the mixed split can contract some N tiles with three products and the rest with one.
     int nt0, nt_end;
+    RowOut out;                  // recompute mode only
 };
 
 // One gradient contraction of the fp8 paths (gx or gy): as BwdAxisBf16 without store mode; B is the
@@ -142,6 +164,21 @@ struct BwdAxisFp8 {
     double *gpart;               // out: [tiles_n][n]
     double *gpart2;              // unused by the gradient (one epilogue)
     float pil;
+};
+
+// The per-block tables of one axis: phase records and, unless seeds is NULL, the seeds of its runs (runs = seed_runs(M)).
+struct AxisTables {
+    const double *c, *sz;        // centres and sizes (sz NULL: size 0)
+    double L;
+    PhaseRec *rec;
+    RunSeed *seeds;
+    int runs;
+};
+
+// One prepared operand of the bf16 row-form contractions (see k_setup): trans = 0: N = u, K = p; 1: N = p, K = u.
+struct PrepBf16 {
+    int Np, Kh;                  // N frequencies rounded up to 256, K half length; Np = 0: nothing
+    unsigned short *B;
 };
 
 // Store-mode basis tables of both axes (bf16 hi and lo, row-major [block][frequency]).
@@ -167,28 +204,29 @@ class TimedLaunch {
 hipError_t launch_fwd_f64(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W, double H,
                           const double *x, const double *y, const double *w, const double *h,
                           double *part, hipStream_t s);
-hipError_t launch_rowform_f64(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s);
+// Row-form contractions, one or two (ax1 NULL: one) in one launch.
+hipError_t launch_rowform_f64(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1,
+                              hipStream_t s);
 // FP32 operands on v_mfma_f32_16x16x4f32 (basis generated in FP64, rounded when stored; FP32
 // accumulation inside a tile, FP64 across tiles).
 hipError_t launch_fwd_f32(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W, double H,
                           const double *x, const double *y, const double *w, const double *h,
                           float *part, hipStream_t s);
-hipError_t launch_rowform_f32(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s);
-// Phase records of both axes (w, h may be NULL for points: size 0).
-hipError_t launch_phase_tables(int64_t n, const double *x, const double *y, const double *w, const double *h,
-                               double W, double H, PhaseRec *tx, PhaseRec *ty, hipStream_t s);
-// Run seeds of one axis from its phase records (runs = seed_runs(M)).
-hipError_t launch_seed_table(int64_t n, int runs, const PhaseRec *tab, RunSeed *seeds, hipStream_t s);
+hipError_t launch_rowform_f32(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1,
+                              hipStream_t s);
+// The tables of both axes in one launch.
+hipError_t launch_axis_tables(int64_t n, const AxisTables &x, const AxisTables &y, hipStream_t s);
+// The same and the prepared operands of the bf16 row-form contractions from a (prep[trans]), in one launch.
+hipError_t launch_setup_bf16(int64_t n, const AxisTables &x, const AxisTables &y, RowForm f, const double *a, int Mu,
+                             int Mp, double W, double H, const PrepBf16 (&prep)[2], hipStream_t s);
 hipError_t launch_fwd_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                            const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
 // Mixed split: the rx x ry low-frequency tiles with k_fwd1_bf16 (three products), the others with
 // the one-product kernel; same partials and plan as launch_fwd_bf16.
 hipError_t launch_fwd_bf16_mix(const FwdPlan &pl, int rx, int ry, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                                const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
-hipError_t launch_prep_bwd_bf16(RowForm f, const double *a, int Mu, int Mp, double W, double H, int trans, int Np,
-                                int Kh, unsigned short *B, hipStream_t s);
 size_t bwd_bf16_operand_elems(int Np, int Kh);   // bf16 elements of one tiled backward operand
-hipError_t launch_bwd_bf16(RowForm f, bool x3, int64_t n, const BwdAxisBf16 &ax, hipStream_t s);
+hipError_t launch_bwd_bf16(RowForm f, bool x3, int64_t n, const BwdAxisBf16 &ax0, const BwdAxisBf16 *ax1, hipStream_t s);
 // Store mode: table rows (n rounded up to 256) and row length (M rounded up to 256); the table of
 // one axis from its phase records (lo table only for x3); the forward from both axes' tables.
 int64_t store_rows(int64_t n);
@@ -204,8 +242,13 @@ hipError_t launch_fwd_bf16_st(const FwdPlan &pl, bool x3, int64_t n, int Mu, int
 hipError_t launch_fwd_fp8(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                           const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
 size_t fp8_operand_bytes(int Np, int Kh);
-hipError_t launch_prep_bwd_fp8(RowForm f, const double *a, int Mu, int Mp, double W, double H, int trans, int Np,
-                               int Kh, unsigned char *B, float *B0, hipStream_t s);
+struct PrepFp8 {
+    int Np, Kh;                  // N frequencies rounded up to 256, K half length
+    unsigned char *B;
+    float *B0;
+};
+hipError_t launch_prep_bwd_fp8(RowForm f, const double *a, int Mu, int Mp, double W, double H, const PrepFp8 (&prep)[2],
+                               hipStream_t s);
 hipError_t launch_bwd_fp8(RowForm f, bool x3, int64_t n, const BwdAxisFp8 &ax, hipStream_t s);
 
 // Sum split-K partials (FP64 or FP32), scale, write a, per-block energy partials.

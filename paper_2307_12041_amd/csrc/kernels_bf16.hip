@@ -63,74 +63,74 @@ __device__ __forceinline__ void split2(float a, float b, unsigned &hi, unsigned 
 
 }  // namespace
 
-// Per-block phase record for one axis (see common.h); rows n .. rows - 1 get zero records.
-__global__ void k_phase_table(int64_t n, int64_t rows, const double *__restrict__ c, const double *__restrict__ sz,
-                              double L, PhaseRec *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows) return;
-    if (i >= n) {
-        out[i] = PhaseRec{};
-        return;
-    }
-    const double szi = sz ? sz[i] : 0.0;
-    const double ta = c[i] / L, tb = szi / (2.0 * L);
-    PhaseRec r;
-    r.ta = ta;
-    r.tb = tb;
-    double s, co;
-    sincospi(reduce_half_turns(ta), &s, &co);
-    r.ca = (float)co; r.sa = (float)s;
-    r.c2ah = (float)(2.0 * co); r.c2al = (float)(2.0 * co - (double)r.c2ah);
-    sincospi(reduce_half_turns(tb), &s, &co);
-    r.cb = (float)co; r.sb = (float)s;
-    r.c2bh = (float)(2.0 * co); r.c2bl = (float)(2.0 * co - (double)r.c2bh);
-    sincospi(reduce_half_turns(32.0 * ta), &s, &co);
-    r.ca32 = (float)co; r.sa32 = (float)s;
-    sincospi(reduce_half_turns(32.0 * tb), &s, &co);
-    r.cb32 = (float)co; r.sb32 = (float)s;
-    r.size = (float)szi;
-    r.pad0 = r.pad1 = r.pad2 = 0.0f;
-    out[i] = r;
-}
+namespace {
 
-// Run seeds of one axis (see RunSeed in common.h): one thread per row walks the runs, rotating the
-// FP64 phasors of u0 alpha and u0 beta by 32 frequencies per run and reseeding them exactly (FP64
-// reduction and sincospi) every 16 runs; rows n .. rows - 1 get zero seeds (an absent block).
-__global__ void k_seed_table(int64_t n, int64_t rows, int runs, const PhaseRec *__restrict__ tab,
-                             RunSeed *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The tables of row i of one axis: its phase record and the seeds of the groups of 16 runs z, z + slices, ... (see PhaseRec
+// and RunSeed in common.h); rows n .. rows - 1 get zeros (an absent block).  The FP64 phasors of u0 alpha and u0 beta are
+// rotated by 32 frequencies per run and evaluated exactly (FP64 reduction and sincospi) at every sixteenth run.
+__device__ __forceinline__ void axis_tables(int64_t i, int64_t n, int64_t rows, const AxisTables &ax, int z, int slices) {
     if (i >= rows) return;
+    RunSeed *__restrict__ seeds = ax.seeds;
     if (i >= n) {
-        for (int r = 0; r < runs; ++r) out[(size_t)r * (size_t)rows + (size_t)i] = RunSeed{0.0f, 0.0f, 0.0f, 0.0f};
+        if (z == 0) ax.rec[i] = PhaseRec{};
+        if (seeds)
+            for (int g = z; 16 * g < ax.runs; g += slices)
+                for (int r = 16 * g; r < min(ax.runs, 16 * g + 16); ++r)
+                    seeds[(size_t)r * (size_t)rows + (size_t)i] = RunSeed{0.0f, 0.0f, 0.0f, 0.0f};
         return;
     }
-    const double ta = tab[i].ta, tb = tab[i].tb;
+    const double szi = ax.sz ? ax.sz[i] : 0.0;
+    const double ta = ax.c[i] / ax.L, tb = szi / (2.0 * ax.L);
     double sa1, ca1, sb1, cb1, sj, cj, sjb, cjb;
     sincospi(reduce_half_turns(ta), &sa1, &ca1);
     sincospi(reduce_half_turns(tb), &sb1, &cb1);
     sincospi(reduce_half_turns(32.0 * ta), &sj, &cj);
     sincospi(reduce_half_turns(32.0 * tb), &sjb, &cjb);
-    double ca = 1.0, sa = 0.0, cb = 1.0, sb = 0.0;   // phasors of u0 alpha and u0 beta
-    for (int r = 0; r < runs; ++r) {
-        if ((r & 15) == 0) {
-            sincospi(reduce_half_turns((double)(32 * r) * ta), &sa, &ca);
-            sincospi(reduce_half_turns((double)(32 * r) * tb), &sb, &cb);
+    if (z == 0) {
+        PhaseRec r;
+        r.ta = ta;
+        r.tb = tb;
+        r.ca = (float)ca1; r.sa = (float)sa1;
+        r.c2ah = (float)(2.0 * ca1); r.c2al = (float)(2.0 * ca1 - (double)r.c2ah);
+        r.cb = (float)cb1; r.sb = (float)sb1;
+        r.c2bh = (float)(2.0 * cb1); r.c2bl = (float)(2.0 * cb1 - (double)r.c2bh);
+        r.ca32 = (float)cj; r.sa32 = (float)sj;
+        r.cb32 = (float)cjb; r.sb32 = (float)sjb;
+        r.size = (float)szi;
+        r.pad0 = r.pad1 = r.pad2 = 0.0f;
+        ax.rec[i] = r;
+    }
+    if (!seeds) return;
+    for (int g = z; 16 * g < ax.runs; g += slices) {
+        double ca, sa, cb, sb;   // phasors of u0 alpha and u0 beta
+        sincospi(reduce_half_turns((double)(512 * g) * ta), &sa, &ca);
+        sincospi(reduce_half_turns((double)(512 * g) * tb), &sb, &cb);
+        for (int r = 16 * g; r < min(ax.runs, 16 * g + 16); ++r) {
+            RunSeed q;
+            q.cf = (float)ca;
+            // the fused products are spelled out, so that a seed's bits do not depend on the surrounding code
+            q.cfm = (float)fma(ca, ca1, sa * sa1);             // cos((u0 - 1) alpha)
+            q.sf = (float)(2.0 * sb);
+            q.sfm = (float)(2.0 * fma(sb, cb1, -(cb * sb1)));  // 2 sin((u0 - 1) beta)
+            seeds[(size_t)r * (size_t)rows + (size_t)i] = q;
+            const double ta2 = fma(ca, cj, -(sa * sj)), tb2 = fma(cb, cjb, -(sb * sjb));
+            sa = fma(ca, sj, sa * cj);
+            ca = ta2;
+            sb = fma(cb, sjb, sb * cjb);
+            cb = tb2;
         }
-        RunSeed q;
-        q.cf = (float)ca;
-        q.cfm = (float)(ca * ca1 + sa * sa1);           // cos((u0 - 1) alpha)
-        q.sf = (float)(2.0 * sb);
-        q.sfm = (float)(2.0 * (sb * cb1 - cb * sb1));   // 2 sin((u0 - 1) beta)
-        out[(size_t)r * (size_t)rows + (size_t)i] = q;
-        const double ta2 = ca * cj - sa * sj, tb2 = cb * cjb - sb * sjb;
-        sa = sa * cj + ca * sj;
-        ca = ta2;
-        sb = sb * cjb + cb * sjb;
-        cb = tb2;
     }
 }
 
-namespace {
+struct TablePair {
+    AxisTables a[2];
+};
+
+// Grid (rows / 256, axes, slices of the runs).  Bound by writing the seeds (4.8 TB/s at two million blocks and 64 runs)
+// where the blocks are many, by one thread's chain of runs where they are few.
+__global__ __launch_bounds__(256) void k_axis_tables(int64_t n, int64_t rows, TablePair P) {
+    axis_tables((int64_t)blockIdx.x * 256 + threadIdx.x, n, rows, blockIdx.y ? P.a[1] : P.a[0], blockIdx.z, gridDim.z);
+}
 
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -1286,12 +1286,14 @@ __device__ __forceinline__ void bwd1_gen_all(Bwd1Ctx<KA> &c, std::integer_sequen
 
 // X3: three products per pair (hi*hi, lo*hi, hi*lo); otherwise one (hi*hi).
 template <bool X3, int KA, int E1, int E2>
-__global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, BwdAxisBf16 ax) {
+__global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf16> P) {
     __shared__ __attribute__((aligned(16))) char smem[2 * BBUF];
+    const bool second = (int)blockIdx.y >= P.tiles0;
+    const BwdAxisBf16 ax = P.pick(second);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, j = lane & 31;
-    const int btile = blockIdx.x, ntile = blockIdx.y + ax.nt0;
+    const int btile = blockIdx.x, ntile = (int)blockIdx.y - (second ? P.tiles0 : 0) + ax.nt0;
     const int64_t i0 = (int64_t)btile * 256 + 64 * wave;
     const int n0 = ntile * BTN;
     const int Q = ax.Kh / 32;
@@ -1408,8 +1410,14 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, BwdAxisBf16 ax) {
         if (n0 == 0) sum += (double)eg.size * (double)g00;   // 2 cos sin vanishes at nn = 0
     }
     if (rvalid) {
-        ax.gpart[(size_t)ntile * (size_t)n + (size_t)ibr] = sum;
-        if constexpr (EGen<E1, E2>::DUAL) ax.gpart2[(size_t)ntile * (size_t)n + (size_t)ibr] = sum2;
+        if (ax.out.r) {
+            const double d = ax.out.dE ? *ax.out.dE : 1.0;
+            ax.out.r[ibr] = d * sum;
+            if constexpr (EGen<E1, E2>::DUAL) if (ax.out.r2) ax.out.r2[ibr] = d * sum2;
+        } else {
+            ax.gpart[(size_t)ntile * (size_t)n + (size_t)ibr] = sum;
+            if constexpr (EGen<E1, E2>::DUAL) ax.gpart2[(size_t)ntile * (size_t)n + (size_t)ibr] = sum2;
+        }
     }
 }
 
@@ -1421,36 +1429,59 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, BwdAxisBf16 ax) {
 // index seg stored at seg ^ ((row / 2) % 8); logical segment seg = 4 half + s holds
 // k = half * Kh + 32 q + 8 s + e (e = 0..7).
 // trans = 0: nn = u, k = p (gx operand, a_up / vt_p);  trans = 1: nn = p, k = u (gy, a_up / wt_u).
-__global__ void k_prep_bwd_bf16(int form, const double *__restrict__ a, int Mu, int Mp, double W, double H,
-                                int trans, int Np, int Kh, unsigned short *__restrict__ B) {
-    const int Q = Kh / 32;
-    const size_t per_tile = (size_t)BBUF / 2;
-    const size_t total = (size_t)(Np / BTN) * (size_t)Q * per_tile;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const size_t tile = idx / per_tile;
-    const int within = (int)(idx % per_tile);
-    const int hl = within / (BARR / 2);
-    const int r = within % (BARR / 2);
-    const int row = r / BKC, pseg = (r % BKC) / 8, e = r % 8;
-    const int seg = pseg ^ ((row >> 1) & 7);
-    const int half = seg >> 2, st = seg & 3;
+// One thread makes the hi and lo segments of 8 values; neighbouring threads take neighbouring segments of a row (trans 0)
+// or neighbouring rows (trans 1), so that a is read along its rows either way.
+__device__ __forceinline__ void prep_segment(size_t idx, int form, const double *__restrict__ a, int Mu, int Mp, double W,
+                                             double H, int trans, const PrepBf16 &P) {
+    const int Q = P.Kh / 32;
+    constexpr int SEGS = BTN * BKC / 8;   // segments of a tile, hi and lo together
+    const size_t tile = idx / SEGS;
+    if (tile >= (size_t)(P.Np / BTN) * (size_t)Q) return;
+    const int within = (int)(idx % SEGS);
+    const int row = trans ? within % BTN : within / 8, seg = trans ? within / BTN : within % 8;
     const int nt = (int)(tile / Q), q = (int)(tile % Q);
     const int nn = nt * BTN + row;
-    const int k = half * Kh + 32 * q + 8 * st + e;
+    const int k0 = (seg >> 2) * P.Kh + 32 * q + 8 * (seg & 3);
     const int Nb = trans ? Mp : Mu, Ka = trans ? Mu : Mp;
-    float out = 0.0f;
-    if (nn < Nb && k < Ka) {
-        const int u = trans ? k : nn, p = trans ? nn : k;
-        const double wt = u ? (double)u * kPi / W : 1.0, vt = p ? (double)p * kPi / H : 1.0;
-        double sc = 1.0;                                  // ROW_POINT_*: a itself
-        if (form == ROW_FIELD) sc = trans ? wt : vt;      // a / (scale of the K axis)
-        else if (form == ROW_POTENTIAL) sc = wt * vt;     // a / (wt_u vt_p)
-        const double v = a[(size_t)u * Mp + p] / sc;
-        const float hv = (float)(__bf16)(float)v;
-        out = hl == 0 ? hv : (float)(__bf16)(float)(v - (double)hv);
+    unsigned hi[4], lo[4];
+    float hv[8], lv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int k = k0 + e;
+        hv[e] = lv[e] = 0.0f;
+        if (nn < Nb && k < Ka) {
+            const int u = trans ? k : nn, p = trans ? nn : k;
+            const double wt = u ? (double)u * kPi / W : 1.0, vt = p ? (double)p * kPi / H : 1.0;
+            double sc = 1.0;                                  // ROW_POINT_*: a itself
+            if (form == ROW_FIELD) sc = trans ? wt : vt;      // a / (scale of the K axis)
+            else if (form == ROW_POTENTIAL) sc = wt * vt;     // a / (wt_u vt_p)
+            const double v = a[(size_t)u * Mp + p] / sc;
+            hv[e] = (float)(__bf16)(float)v;
+            lv[e] = (float)(__bf16)(float)(v - (double)hv[e]);
+        }
     }
-    B[idx] = __builtin_bit_cast(unsigned short, (__bf16)out);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        hi[e] = pack_bf16(hv[2 * e], hv[2 * e + 1]);
+        lo[e] = pack_bf16(lv[2 * e], lv[2 * e + 1]);
+    }
+    char *dst = (char *)P.B + tile * (size_t)BBUF + row * BROW + ((seg ^ ((row >> 1) & 7)) << 4);
+    *(u32x4 *)dst = u32x4{hi[0], hi[1], hi[2], hi[3]};
+    *(u32x4 *)(dst + BARR) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+}
+
+struct PrepPair {
+    PrepBf16 p[2];
+};
+
+// What a bf16 row-form contraction needs, in one launch: grid y = 0, 1 the phase records of the x and the y axis, 2, 3 the
+// prepared operands of trans 0 and 1; the threads of grid x beyond a part's own range have nothing to do.
+__global__ __launch_bounds__(256) void k_setup(int64_t n, int64_t rows, TablePair T, int form,
+                                               const double *__restrict__ a, int Mu, int Mp, double W, double H,
+                                               PrepPair P) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.y < 2) axis_tables(i, n, rows, blockIdx.y ? T.a[1] : T.a[0], 0, 1);
+    else prep_segment((size_t)i, form, a, Mu, Mp, W, H, (int)blockIdx.y - 2, blockIdx.y == 3 ? P.p[1] : P.p[0]);
 }
 
 // ================================================================================================
@@ -1574,20 +1605,29 @@ __global__ __launch_bounds__(512) void k_fwd_bf16_st(int Mu, int Mp, StoreTables
 
 }  // namespace
 
-hipError_t launch_phase_tables(int64_t n, const double *x, const double *y, const double *w, const double *h,
-                               double W, double H, PhaseRec *tx, PhaseRec *ty, hipStream_t s) {
+hipError_t launch_axis_tables(int64_t n, const AxisTables &x, const AxisTables &y, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t rows = phase_rows(n);
-    const unsigned g = (unsigned)((rows + 255) / 256);
-    hipLaunchKernelGGL(k_phase_table, dim3(g), dim3(256), 0, s, n, rows, x, w, W, tx);
-    hipLaunchKernelGGL(k_phase_table, dim3(g), dim3(256), 0, s, n, rows, y, h, H, ty);
+    // the runs of a block go to several threads where one thread per block would leave the chip short of waves (fewer than
+    // eight of them per SIMD in all)
+    const int runs = x.seeds ? (x.runs > y.runs ? x.runs : y.runs) : 0;
+    const int slices = runs > 16 && 2 * rows < 8 * 64 * 1024 ? (runs + 15) / 16 : 1;
+    hipLaunchKernelGGL(k_axis_tables, dim3((unsigned)((rows + 255) / 256), 2, (unsigned)slices), dim3(256), 0, s, n, rows,
+                       TablePair{{x, y}});
     return hipGetLastError();
 }
 
-hipError_t launch_seed_table(int64_t n, int runs, const PhaseRec *tab, RunSeed *seeds, hipStream_t s) {
+hipError_t launch_setup_bf16(int64_t n, const AxisTables &x, const AxisTables &y, RowForm f, const double *a, int Mu,
+                             int Mp, double W, double H, const PrepBf16 (&prep)[2], hipStream_t s) {
     if (n == 0) return hipSuccess;
     const int64_t rows = phase_rows(n);
-    hipLaunchKernelGGL(k_seed_table, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, n, rows, runs, tab, seeds);
+    size_t threads = (size_t)rows;
+    for (const PrepBf16 &p : prep) {
+        const size_t segs = bwd_bf16_operand_elems(p.Np, p.Kh) / 16;
+        if (segs > threads) threads = segs;
+    }
+    hipLaunchKernelGGL(k_setup, dim3((unsigned)((threads + 255) / 256), prep[1].Np ? 4 : 3), dim3(256), 0, s, n, rows,
+                       TablePair{{x, y}}, (int)f, a, Mu, Mp, W, H, PrepPair{{prep[0], prep[1]}});
     return hipGetLastError();
 }
 
@@ -1619,48 +1659,50 @@ hipError_t launch_fwd_bf16_mix(const FwdPlan &pl, int rx, int ry, int64_t n, int
     return hipGetLastError();
 }
 
-hipError_t launch_prep_bwd_bf16(RowForm f, const double *a, int Mu, int Mp, double W, double H, int trans, int Np,
-                                int Kh, unsigned short *B, hipStream_t s) {
-    const size_t total = bwd_bf16_operand_elems(Np, Kh);
-    hipLaunchKernelGGL(k_prep_bwd_bf16, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (int)f, a, Mu, Mp, W,
-                       H, trans, Np, Kh, B);
-    return hipGetLastError();
-}
-
 size_t bwd_bf16_operand_elems(int Np, int Kh) { return (size_t)(Np / BTN) * (size_t)(Kh / 32) * (size_t)(BBUF / 2); }
 
 namespace {
 template <int KA, int E1, int E2>
-hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax, hipStream_t s) {
-    const int tiles_n = (ax.Nb + BTN - 1) / BTN;
-    const int nt_end = ax.nt_end > 0 ? ax.nt_end : tiles_n;
-    if (ax.nt0 < 0 || nt_end > tiles_n || ax.nt0 >= nt_end) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((n + 255) / 256), (unsigned)(nt_end - ax.nt0));
-    if (x3) hipLaunchKernelGGL((k_bwd1_bf16<true, KA, E1, E2>), grid, dim3(256), 0, s, n, ax);
-    else hipLaunchKernelGGL((k_bwd1_bf16<false, KA, E1, E2>), grid, dim3(256), 0, s, n, ax);
+hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax0, const BwdAxisBf16 *ax1, hipStream_t s) {
+    AxisPair<BwdAxisBf16> P{{ax0, ax1 ? *ax1 : ax0}, 0};
+    int tiles[2] = {0, 0};
+    for (int k = 0; k < (ax1 ? 2 : 1); ++k) {
+        const BwdAxisBf16 &ax = P.a[k];
+        const int tiles_n = (ax.Nb + BTN - 1) / BTN;
+        const int nt_end = ax.nt_end > 0 ? ax.nt_end : tiles_n;
+        if (ax.nt0 < 0 || nt_end > tiles_n || ax.nt0 >= nt_end || (ax.out.r && tiles_n > 1)) return hipErrorInvalidValue;
+        tiles[k] = nt_end - ax.nt0;
+    }
+    P.tiles0 = tiles[0];
+    dim3 grid((unsigned)((n + 255) / 256), (unsigned)(tiles[0] + tiles[1]));
+    if (x3) hipLaunchKernelGGL((k_bwd1_bf16<true, KA, E1, E2>), grid, dim3(256), 0, s, n, P);
+    else hipLaunchKernelGGL((k_bwd1_bf16<false, KA, E1, E2>), grid, dim3(256), 0, s, n, P);
     return hipGetLastError();
 }
 }  // namespace
 
-hipError_t launch_bwd_bf16(RowForm f, bool x3, int64_t n, const BwdAxisBf16 &ax, hipStream_t s) {
+hipError_t launch_bwd_bf16(RowForm f, bool x3, int64_t n, const BwdAxisBf16 &ax, const BwdAxisBf16 *ax1, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (ax.tab_h) {
-        // store mode (gradient only): one-dimensional XCD-aware grid over (block tile, N tile)
-        if (f != ROW_FIELD || ax.tiles_b != (int)((n + 255) / 256) || ax.tiles_n != (ax.Nb + BTN - 1) / BTN ||
-            ax.tab_ld < 2 * ax.Kh || (x3 && !ax.tab_l))
-            return hipErrorInvalidValue;
-        const unsigned g = (unsigned)((ax.tiles_b + 7) / 8 * 8 * ax.tiles_n);
-        if (x3) hipLaunchKernelGGL(k_bwd_bf16_st<true>, dim3(g), dim3(512), 0, s, n, ax);
-        else hipLaunchKernelGGL(k_bwd_bf16_st<false>, dim3(g), dim3(512), 0, s, n, ax);
+        // store mode (gradient only): one-dimensional XCD-aware grid over (block tile, N tile), a launch per contraction
+        for (const BwdAxisBf16 *p : {&ax, ax1}) {
+            if (!p) continue;
+            if (f != ROW_FIELD || p->tiles_b != (int)((n + 255) / 256) || p->tiles_n != (p->Nb + BTN - 1) / BTN ||
+                p->tab_ld < 2 * p->Kh || (x3 && !p->tab_l))
+                return hipErrorInvalidValue;
+            const unsigned g = (unsigned)((p->tiles_b + 7) / 8 * 8 * p->tiles_n);
+            if (x3) hipLaunchKernelGGL(k_bwd_bf16_st<true>, dim3(g), dim3(512), 0, s, n, *p);
+            else hipLaunchKernelGGL(k_bwd_bf16_st<false>, dim3(g), dim3(512), 0, s, n, *p);
+        }
         return hipGetLastError();
     }
     switch (f) {
-        case ROW_FIELD: return launch_rowform_bf16<RUN_SINDIFF, RUN_COSDIFF, -1>(x3, n, ax, s);
-        case ROW_POTENTIAL: return launch_rowform_bf16<RUN_SINDIFF, RUN_SINDIFF, -1>(x3, n, ax, s);
+        case ROW_FIELD: return launch_rowform_bf16<RUN_SINDIFF, RUN_COSDIFF, -1>(x3, n, ax, ax1, s);
+        case ROW_POTENTIAL: return launch_rowform_bf16<RUN_SINDIFF, RUN_SINDIFF, -1>(x3, n, ax, ax1, s);
         case ROW_POINT_DUAL:
-            if (!ax.gpart2) return hipErrorInvalidValue;
-            return launch_rowform_bf16<RUN_COS, RUN_COS, RUN_WSIN>(x3, n, ax, s);
-        case ROW_POINT_WSIN: return launch_rowform_bf16<RUN_COS, RUN_WSIN, -1>(x3, n, ax, s);
+            if (!ax.out.r && !ax.gpart2) return hipErrorInvalidValue;
+            return launch_rowform_bf16<RUN_COS, RUN_COS, RUN_WSIN>(x3, n, ax, ax1, s);
+        case ROW_POINT_WSIN: return launch_rowform_bf16<RUN_COS, RUN_WSIN, -1>(x3, n, ax, ax1, s);
     }
     return hipErrorInvalidValue;
 }

@@ -307,8 +307,11 @@ __global__ __launch_bounds__(256) void k_fwd_mat(int64_t n, int Mu, int Mp, doub
 // its next operand chunk, which sit between barriers.
 // ------------------------------------------------------------------------------------------------
 template <typename T, int TB, int TN, int KK, int KA_KIND, int EP1, int EP2>
-__global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, BwdAxis ax) {
+__global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis> P) {
     typedef typename Mat<T>::v4 v4;
+    const bool second = (int)blockIdx.y >= P.tiles0;
+    const BwdAxis ax = P.pick(second);
+    const int ntile = (int)blockIdx.y - (second ? P.tiles0 : 0);
     constexpr int LB = TB + 1, LN = TN + 1;
     constexpr int HALF = TN / 2;
     static_assert(TB == 128 && TN == 128 && KK == 32, "LDS reuse below assumes this tile");
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, BwdAxis ax) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t ib0 = (int64_t)blockIdx.x * TB;
-    const int n0 = (int)blockIdx.y * TN;
+    const int n0 = ntile * TN;
     const int wi0 = (wave >> 1) * WI, wc = wave & 1, wj0 = wc * WJ;
     const int gi = tid % TB, grun = tid / TB;
     const int64_t ib = ib0 + gi;
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, BwdAxis ax) {
 
     // Epilogue(s): row dot with the epilogue basis, one N half at a time; the 16 lanes that share
     // a row are summed by a fixed butterfly, the two column waves in fixed order.
-    auto epilogue = [&](auto kind_tag, double *__restrict__ gpart) {
+    auto epilogue = [&](auto kind_tag, double *__restrict__ gpart, double *__restrict__ out) {
         constexpr int EK = decltype(kind_tag)::value;
         double rs[SI][4];
 #pragma unroll
@@ -419,11 +422,14 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, BwdAxis ax) {
                 for (int r = 0; r < 4; ++r) red[wc * TB + wi0 + a * 16 + Mat<T>::row(lane, r)] = rs[a][r];
         }
         __syncthreads();
-        if (tid < TB && ib0 + tid < n)
-            gpart[(size_t)blockIdx.y * (size_t)n + (size_t)(ib0 + tid)] = red[tid] + red[TB + tid];
+        if (tid < TB && ib0 + tid < n) {
+            const double v = red[tid] + red[TB + tid];
+            if (!ax.out.r) gpart[(size_t)ntile * (size_t)n + (size_t)(ib0 + tid)] = v;
+            else if (out) out[ib0 + tid] = (ax.out.dE ? *ax.out.dE : 1.0) * v;
+        }
     };
-    epilogue(std::integral_constant<int, EP1>{}, ax.gpart);
-    if constexpr (EP2 >= 0) epilogue(std::integral_constant<int, (EP2 >= 0 ? EP2 : 0)>{}, ax.gpart2);
+    epilogue(std::integral_constant<int, EP1>{}, ax.gpart, ax.out.r);
+    if constexpr (EP2 >= 0) epilogue(std::integral_constant<int, (EP2 >= 0 ? EP2 : 0)>{}, ax.gpart2, ax.out.r2);
 }
 
 template <typename T>
@@ -442,23 +448,25 @@ hipError_t launch_fwd_mat(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W
 }
 
 template <typename T, int KA_KIND, int EP1, int EP2>
-hipError_t launch_rowform(const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s) {
+hipError_t launch_rowform(const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1, hipStream_t s) {
     if (!(pl.tb == 128 && pl.tn == 128 && pl.kk == 32)) return hipErrorInvalidValue;
     if (n == 0) return hipSuccess;
-    const int tiles_n = (ax.Nb + pl.tn - 1) / pl.tn;
-    const int64_t tiles_b = (n + pl.tb - 1) / pl.tb;
-    dim3 grid((unsigned)tiles_b, tiles_n);
-    hipLaunchKernelGGL((k_bwd_mat<T, 128, 128, 32, KA_KIND, EP1, EP2>), grid, dim3(256), 0, s, n, ax);
+    AxisPair<BwdAxis> P{{ax0, ax1 ? *ax1 : ax0}, (ax0.Nb + pl.tn - 1) / pl.tn};
+    const int tiles1 = ax1 ? (ax1->Nb + pl.tn - 1) / pl.tn : 0;
+    if ((ax0.out.r && P.tiles0 > 1) || (ax1 && ax1->out.r && tiles1 > 1)) return hipErrorInvalidValue;
+    dim3 grid((unsigned)((n + pl.tb - 1) / pl.tb), (unsigned)(P.tiles0 + tiles1));
+    hipLaunchKernelGGL((k_bwd_mat<T, 128, 128, 32, KA_KIND, EP1, EP2>), grid, dim3(256), 0, s, n, P);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_rowform_kind(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s) {
+hipError_t launch_rowform_kind(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, const BwdAxis *ax1,
+                               hipStream_t s) {
     switch (f) {
-        case ROW_FIELD: return launch_rowform<T, RUN_SINDIFF, RUN_COSDIFF, -1>(pl, n, ax, s);
-        case ROW_POTENTIAL: return launch_rowform<T, RUN_SINDIFF, RUN_SINDIFF, -1>(pl, n, ax, s);
-        case ROW_POINT_DUAL: return launch_rowform<T, RUN_COS, RUN_COS, RUN_WSIN>(pl, n, ax, s);
-        case ROW_POINT_WSIN: return launch_rowform<T, RUN_COS, RUN_WSIN, -1>(pl, n, ax, s);
+        case ROW_FIELD: return launch_rowform<T, RUN_SINDIFF, RUN_COSDIFF, -1>(pl, n, ax, ax1, s);
+        case ROW_POTENTIAL: return launch_rowform<T, RUN_SINDIFF, RUN_SINDIFF, -1>(pl, n, ax, ax1, s);
+        case ROW_POINT_DUAL: return launch_rowform<T, RUN_COS, RUN_COS, RUN_WSIN>(pl, n, ax, ax1, s);
+        case ROW_POINT_WSIN: return launch_rowform<T, RUN_COS, RUN_WSIN, -1>(pl, n, ax, ax1, s);
     }
     return hipErrorInvalidValue;
 }
@@ -473,11 +481,13 @@ hipError_t launch_fwd_f32(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W
                           const double *y, const double *w, const double *h, float *part, hipStream_t s) {
     return launch_fwd_mat<float>(pl, n, Mu, Mp, W, H, x, y, w, h, part, s);
 }
-hipError_t launch_rowform_f64(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s) {
-    return launch_rowform_kind<double>(f, pl, n, ax, s);
+hipError_t launch_rowform_f64(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1,
+                              hipStream_t s) {
+    return launch_rowform_kind<double>(f, pl, n, ax0, ax1, s);
 }
-hipError_t launch_rowform_f32(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax, hipStream_t s) {
-    return launch_rowform_kind<float>(f, pl, n, ax, s);
+hipError_t launch_rowform_f32(RowForm f, const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1,
+                              hipStream_t s) {
+    return launch_rowform_kind<float>(f, pl, n, ax0, ax1, s);
 }
 
 }  // namespace pp

@@ -93,9 +93,17 @@ __device__ __forceinline__ int f8_seg(int row, int seg) { return (seg ^ ((row >>
 }  // namespace
 
 // One thread per (N tile, chunk, row): the 64 values of its row, their scale, hi and lo codes.
-// form / trans / sc as in k_prep_bwd_bf16: trans = 0: nn = u, k = p; trans = 1: nn = p, k = u.
-__global__ void k_prep_bwd_fp8(int form, const double *__restrict__ a, int Mu, int Mp, double W, double H,
-                               int trans, int Np, int Kh, unsigned char *__restrict__ B, float *__restrict__ B0) {
+// form / trans / sc as in prep_segment (bf16): trans = 0: nn = u, k = p; trans = 1: nn = p, k = u.  Grid y: trans.
+struct PrepPair8 {
+    PrepFp8 p[2];
+};
+
+__global__ __launch_bounds__(256) void k_prep_bwd_fp8(int form, const double *__restrict__ a, int Mu, int Mp, double W,
+                                                      double H, PrepPair8 P) {
+    const int trans = blockIdx.y;
+    const int Np = trans ? P.p[1].Np : P.p[0].Np, Kh = trans ? P.p[1].Kh : P.p[0].Kh;
+    unsigned char *__restrict__ B = trans ? P.p[1].B : P.p[0].B;
+    float *__restrict__ B0 = trans ? P.p[1].B0 : P.p[0].B0;
     const int Q = Kh / 32;
     const int64_t rows_total = (int64_t)(Np / F8_TN) * Q * F8_TN;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -116,7 +124,7 @@ __global__ void k_prep_bwd_fp8(int form, const double *__restrict__ a, int Mu, i
     };
     float v[64];
     float m = 0.0f;
-#pragma unroll 8
+#pragma unroll
     for (int c = 0; c < 64; ++c) {
         const int k = (c >> 5) * Kh + 32 * q + (c & 31);
         v[c] = k == 0 ? 0.0f : (float)value(k);
@@ -629,12 +637,16 @@ hipError_t launch_fwd_fp8(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp,
 
 size_t fp8_operand_bytes(int Np, int Kh) { return (size_t)(Np / F8_TN) * (size_t)(Kh / 32) * (size_t)F8_TILE; }
 
-hipError_t launch_prep_bwd_fp8(RowForm f, const double *a, int Mu, int Mp, double W, double H, int trans, int Np,
-                               int Kh, unsigned char *B, float *B0, hipStream_t s) {
-    const int64_t rows = (int64_t)(Np / F8_TN) * (Kh / 32) * F8_TN;
+hipError_t launch_prep_bwd_fp8(RowForm f, const double *a, int Mu, int Mp, double W, double H, const PrepFp8 (&prep)[2],
+                               hipStream_t s) {
+    int64_t rows = 0;
+    for (const PrepFp8 &p : prep) {
+        const int64_t r = (int64_t)(p.Np / F8_TN) * (p.Kh / 32) * F8_TN;
+        if (r > rows) rows = r;
+    }
     if (rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_prep_bwd_fp8, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, (int)f, a, Mu, Mp, W, H,
-                       trans, Np, Kh, B, B0);
+    hipLaunchKernelGGL(k_prep_bwd_fp8, dim3((unsigned)((rows + 255) / 256), 2), dim3(256), 0, s, (int)f, a, Mu, Mp, W, H,
+                       PrepPair8{{prep[0], prep[1]}});
     return hipGetLastError();
 }
 
