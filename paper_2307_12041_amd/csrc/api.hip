@@ -113,6 +113,13 @@ BwdPlan bwd_plan(const pp_problem &P) {
     } else {
         pl.tb = 128; pl.tn = 128; pl.kk = 32;
     }
+    pl.slots_nx = (P.Mu + pl.tn - 1) / pl.tn;
+    pl.slots_ny = (P.Mp + pl.tn - 1) / pl.tn;
+    // FP32: N tiles of 256 (twice the MFMAs per generated value) where they pad no more columns than tiles of 128 and leave
+    // every CU four workgroups
+    if (P.precision == PP_FP32 && pl.slots_nx % 2 == 0 && pl.slots_ny % 2 == 0 &&
+        (P.n + pl.tb - 1) / pl.tb * ((pl.slots_nx + pl.slots_ny) / 2) >= 1024)
+        pl.tn = 256;
     pl.tiles_b = (P.n + pl.tb - 1) / pl.tb;
     pl.tiles_nx = (P.Mu + pl.tn - 1) / pl.tn;
     pl.tiles_ny = (P.Mp + pl.tn - 1) / pl.tn;
@@ -179,9 +186,9 @@ Layout layout(const pp_problem &P) {
         L.bx = off;  off = align_up(off + MM * b.bmat_elem);
         L.by = off;  off = align_up(off + MM * b.bmat_elem);
     }
-    L.gpx = off; off = align_up(off + (size_t)b.tiles_nx * (size_t)P.n * sizeof(double));
-    L.gpy = off; off = align_up(off + (size_t)b.tiles_ny * (size_t)P.n * sizeof(double));
-    L.gpz = off; off = align_up(off + (size_t)b.tiles_nx * (size_t)P.n * sizeof(double));
+    L.gpx = off; off = align_up(off + (size_t)b.slots_nx * (size_t)P.n * sizeof(double));
+    L.gpy = off; off = align_up(off + (size_t)b.slots_ny * (size_t)P.n * sizeof(double));
+    L.gpz = off; off = align_up(off + (size_t)b.slots_nx * (size_t)P.n * sizeof(double));
     L.bwd_bytes = off;
     L.total = L.fwd_bytes > L.bwd_bytes ? L.fwd_bytes : L.bwd_bytes;
     return L;

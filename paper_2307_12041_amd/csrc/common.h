@@ -34,6 +34,7 @@ struct BwdPlan {
     int64_t tiles_b;     // ceil(n / tb)
     int tiles_nx;        // ceil(Mu / tn)  (gx: N = u)
     int tiles_ny;        // ceil(Mp / tn)  (gy: N = p)
+    int slots_nx, slots_ny;   // partial sums per block that the workspace holds
     size_t bmat_elem;    // bytes per element of the prepared backward operand matrices
 };
 

@@ -11,10 +11,17 @@
 //   v_mfma_f64_16x16x4: D[i][j] in lane j + 16 (i % 4), element i / 4;
 //   v_mfma_f32_16x16x4: D[i][j] in lane j + 16 (i / 4), element i % 4.
 //
-// Basis generation: for a block edge e and frequency k, the phase k*pi*e/L is carried in half
-// turns.  A run of consecutive frequencies starts from an FP64 seed, reduced to [-1, 1] half
-// turns before sincospi, and continues by rotating the (cos, sin) pair by the one-step phasor.
-// Runs are at most 32 long, so the rotation error stays at a few ulp.
+// What bounds these kernels (gfx950, measured with a kernel of MFMAs and VALU instructions alone): the FP64 and FP32 MFMAs run
+// on the vector units, so nothing issues beside them.  A v_mfma_f64_16x16x4 takes 65-68 cycles, a v_mfma_f32_16x16x4 33, and every
+// VALU instruction of any type, of the same or of another wave of the SIMD, adds 4.3 cycles, or about 8 where it
+// alternates with another wave's MFMAs, plus some 12 at each change from MFMA to VALU in a wave.  Hence: as few VALU
+// instructions per MFMA as possible (operand tiles copied straight into LDS, seeds by a short polynomial and shared between
+// threads, long runs, wide tiles for the shorter FP32 MFMAs), and the generator in phases of its own at raised wave
+// priority, so that it is not dealt between another wave's MFMAs one instruction at a time.
+//
+// Basis generation: every value comes from FP64 three-term recurrences f_{k+1} = 2 cos(t) f_k - f_{k-1} over runs of at most 32
+// frequencies that start from exactly reduced FP64 seeds: sine differences as 2 cos(k a) sin(k b) and cosine
+// differences as -2 sin(k a) sin(k b) with a = pi c / L, b = pi size / (2L) for centre c (no cancellation for narrow blocks).
 #include <type_traits>
 
 #include "common.h"
@@ -39,252 +46,248 @@ template <> struct Mat<float> {
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-__device__ __forceinline__ double reduce_half_turns(double t) { return t - 2.0 * rint(0.5 * t); }
+// sin(pi t) and cos(pi t), |t| < 2^50: t = q / 2 + f exactly with an integer q (its low bits are read off the sum that
+// rounds it) and |f| <= 1/4, then the Taylor polynomials of sin(pi f) and cos(pi f) (coefficients pi^j / j!, rounded; the first
+// term left out is below 2^-58 of the result).  An infinite or NaN t gives NaN.
+__device__ __forceinline__ void sincospi_seed64(double t, double &s, double &c) {
+    const double magic = 6755399441055744.0;   // 1.5 * 2^52
+    const double d = fma(2.0, t, magic);
+    const unsigned q = (unsigned)__builtin_bit_cast(unsigned long long, d);
+    const double f = fma(-0.5, d - magic, t);
+    const double x = f * f;
+    double p = 7.95205400147551261e-07, r = 4.30306958703294729e-06;
+    p = fma(p, x, -2.19153534478302173e-05); r = fma(r, x, -1.04638104924845705e-04);
+    p = fma(p, x, 4.66302805767612554e-04);  r = fma(r, x, 1.92957430940392314e-03);
+    p = fma(p, x, -7.37043094571435044e-03); r = fma(r, x, -2.58068913900140612e-02);
+    p = fma(p, x, 8.21458866111282326e-02);  r = fma(r, x, 2.35330630358893206e-01);
+    p = fma(p, x, -5.99264529320792105e-01); r = fma(r, x, -1.33526276885458950e+00);
+    p = fma(p, x, 2.55016403987734552e+00);  r = fma(r, x, 4.05871212641676848e+00);
+    p = fma(p, x, -5.16771278004997026e+00); r = fma(r, x, -4.93480220054467900e+00);
+    p = fma(p, x, 3.14159265358979312e+00);  r = fma(r, x, 1.0);
+    p *= f;
+    const double s0 = (q & 1u) ? r : p, c0 = (q & 1u) ? p : r;
+    // quarter turns: (s, c), (c, -s), (-s, -c), (-c, s)
+    const unsigned long long ns = (unsigned long long)(q & 2u) << 62, nc = (unsigned long long)((q + 1u) & 2u) << 62;
+    s = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, s0) ^ ns);
+    c = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, c0) ^ nc);
+}
 
-struct EdgeRot {
-    double cp, sp, cm, sm;      // current phasors of the + and - edges
-    double c1p, s1p, c1m, s1m;  // one-frequency-step phasors
-    __device__ __forceinline__ void init(double c, double sz, double L, int k0) {
-        const double tp = (c + 0.5 * sz) / L;
-        const double tm = (c - 0.5 * sz) / L;
-        sincospi(reduce_half_turns((double)k0 * tp), &sp, &cp);
-        sincospi(reduce_half_turns((double)k0 * tm), &sm, &cm);
-        sincospi(reduce_half_turns(tp), &s1p, &c1p);
-        sincospi(reduce_half_turns(tm), &s1m, &c1m);
-    }
-    __device__ __forceinline__ void step() {
-        double t = cp * c1p - sp * s1p;
-        sp = sp * c1p + cp * s1p;
-        cp = t;
-        t = cm * c1m - sm * s1m;
-        sm = sm * c1m + cm * s1m;
-        cm = t;
-    }
-};
-
-// One phasor of a point (centre) coordinate: cos and sin of w_k c for consecutive k.
-struct PointRot {
-    double c, s, c1, s1;
-    __device__ __forceinline__ void init(double x, double L, int k0) {
-        const double t = x / L;
-        sincospi(reduce_half_turns((double)k0 * t), &s, &c);
-        sincospi(reduce_half_turns(t), &s1, &c1);
-    }
-    __device__ __forceinline__ void step() {
-        const double t = c * c1 - s * s1;
-        s = s * c1 + c * s1;
+struct Phasor {
+    double c, s;
+    __device__ __forceinline__ void set(double t) { sincospi_seed64(t, s, c); }
+    __device__ __forceinline__ void rotate(const Phasor &r) {
+        const double t = fma(c, r.c, -(s * r.s));
+        s = fma(s, r.c, c * r.s);
         c = t;
     }
 };
 
-// R consecutive values of one kind (RunKind) for one block, written at dst[k*stride] (generated in FP64,
-// rounded to T when stored).
-template <int KIND, int R, typename T>
-__device__ __forceinline__ void gen_run(double c, double sz, double L, int k0, bool valid, T *dst, int stride) {
-    if (!valid) {
-#pragma unroll
-        for (int k = 0; k < R; ++k) dst[k * stride] = (T)0;
-        return;
+// One factor of a basis value over consecutive frequencies: f and the value before it.
+struct Rec {
+    double f, fm, t2;
+    // cos (or sin) of k theta from the phasor of k theta and the one of theta
+    __device__ __forceinline__ void start_cos(const Phasor &p, const Phasor &step) {
+        f = p.c; fm = fma(p.c, step.c, p.s * step.s); t2 = 2.0 * step.c;
     }
-    if constexpr (KIND == RUN_SINDIFF || KIND == RUN_COSDIFF) {
-        EdgeRot r;
-        r.init(c, sz, L, k0);
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if constexpr (KIND == RUN_SINDIFF)
-                dst[k * stride] = (T)((k0 + k == 0) ? sz : (r.sp - r.sm));
-            else
-                dst[k * stride] = (T)(r.cp - r.cm);
-            r.step();
-        }
-    } else {
-        PointRot r;
-        r.init(c, L, k0);
-        const double pil = kPi / L;
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if constexpr (KIND == RUN_COS)
-                dst[k * stride] = (T)r.c;
-            else
-                dst[k * stride] = (T)((double)(k0 + k) * pil * r.s);
-            r.step();
-        }
+    __device__ __forceinline__ void start_sin(const Phasor &p, const Phasor &step) {
+        f = p.s; fm = fma(p.s, step.c, -(p.c * step.s)); t2 = 2.0 * step.c;
     }
-}
-
-// A run of R consecutive frequencies of one block that moves on by J frequencies every K chunk (the
-// row-form contraction, where a thread keeps its block for the whole K loop), for the K-side kinds
-// RUN_SINDIFF (the product form 2 cos(k a) sin(k b), a = pi c / L, b = pi size / (2L)) and RUN_COS
-// (cos(k a), a = pi c / L).  The phasors e^{i k0 a} (and e^{i k0 b}) at the run's first frequency,
-// the one-frequency step and the J-frequency jump come from FP64 sincospi of exactly reduced
-// arguments once; each run is then produced by the three-term recurrence f_{k+1} = 2 cos(t) f_k -
-// f_{k-1} of each factor, and after each chunk the seed phasors are rotated by the jump instead of
-// being evaluated again.
-template <int KIND>
-struct KRun {
-    static_assert(KIND == RUN_SINDIFF || KIND == RUN_COS, "K-side kinds of the row-form contraction");
-    static constexpr bool kProd = KIND == RUN_SINDIFF;
-    double ca, sa, cb, sb;        // seed phasors at the run's first frequency (b: RUN_SINDIFF only)
-    double c1a, s1a, c1b, s1b;    // one-frequency step
-    double cja, sja, cjb, sjb;    // J-frequency jump
-    double sz;
-
-    __device__ __forceinline__ void init(double c, double size, double L, int k0, int J) {
-        sz = size;
-        const double ta = c / L;
-        sincospi(reduce_half_turns((double)k0 * ta), &sa, &ca);
-        sincospi(reduce_half_turns(ta), &s1a, &c1a);
-        sincospi(reduce_half_turns((double)J * ta), &sja, &cja);
-        if constexpr (kProd) {
-            const double tb = 0.5 * size / L;
-            sincospi(reduce_half_turns((double)k0 * tb), &sb, &cb);
-            sincospi(reduce_half_turns(tb), &s1b, &c1b);
-            sincospi(reduce_half_turns((double)J * tb), &sjb, &cjb);
-        }
-    }
-
-    // The R values at frequencies k0 .. k0 + R - 1, written at dst[k * stride] (rounded to T).
-    template <int R, typename T>
-    __device__ __forceinline__ void gen(int k0, bool valid, T *dst, int stride) const {
-        if (!valid) {
-#pragma unroll
-            for (int k = 0; k < R; ++k) dst[k * stride] = (T)0;
-            return;
-        }
-        double C = ca, Cm = ca * c1a + sa * s1a;                  // cos(k0 a), cos((k0 - 1) a)
-        const double ta2 = 2.0 * c1a;
-        double S = 0.0, Sm = 0.0, tb2 = 0.0;
-        if constexpr (kProd) {
-            S = 2.0 * sb;                                         // 2 sin(k0 b), 2 sin((k0 - 1) b)
-            Sm = 2.0 * (sb * c1b - cb * s1b);
-            tb2 = 2.0 * c1b;
-        }
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            if constexpr (kProd)
-                dst[k * stride] = (T)((k0 + k == 0) ? sz : C * S);
-            else
-                dst[k * stride] = (T)C;
-            const double Cn = fma(ta2, C, -Cm);
-            Cm = C;
-            C = Cn;
-            if constexpr (kProd) {
-                const double Sn = fma(tb2, S, -Sm);
-                Sm = S;
-                S = Sn;
-            }
-        }
-    }
-
-    __device__ __forceinline__ void jump() {
-        const double t = ca * cja - sa * sja;
-        sa = sa * cja + ca * sja;
-        ca = t;
-        if constexpr (kProd) {
-            const double u = cb * cjb - sb * sjb;
-            sb = sb * cjb + cb * sjb;
-            cb = u;
-        }
+    __device__ __forceinline__ void next() {
+        const double n = fma(t2, f, -fm);
+        fm = f;
+        f = n;
     }
 };
 
-// R consecutive sine-difference integrals S_k = sin(w_k x+) - sin(w_k x-) of one block (S_0 = its
-// size), k = k0 .. k0 + R - 1, in the product form 2 cos(k a) sin(k b), a = pi c / L,
-// b = pi size / (2L), each factor by its three-term recurrence f_{k+1} = 2 cos(t) f_k - f_{k-1}
-// from FP64 seeds at k0 and k0 - 1: two FMAs and one product per value (two phasor rotations cost
-// eight), with no cancellation for narrow blocks.  Written at dst[k * stride], rounded to T.
-template <int R, typename T>
-__device__ __forceinline__ void gen_sindiff(double c, double sz, double L, int k0, bool valid, T *dst, int stride) {
-    if (!valid) {
+// Runs of one block's (or point's) basis values of one kind along one axis: the phasors of the first frequency, of one
+// frequency and of the jump from a run to the thread's next one.  A thread group shares the last two: `groups` threads per
+// block evaluate them in turn and exchange them through LDS.
+template <int KIND>
+struct BlockRuns {
+    static constexpr bool kSize = KIND == RUN_SINDIFF || KIND == RUN_COSDIFF;
+    Phasor pa, pb, step_a, step_b, jump_a, jump_b;
+    double size;
+
+    // Every thread of the workgroup calls this; ph: LDS for 4 phasors per block; i: the block's index of `blocks`.
+    template <int GROUPS, int BLOCKS>
+    __device__ __forceinline__ void init(double c, double sz, double L, int k0, int J, double2 *ph, int i, int group) {
+        const double ta = c / L, tb = 0.5 * sz / L;
+        size = sz;
+        pa.set((double)k0 * ta);
+        if constexpr (kSize) pb.set((double)k0 * tb);
+        constexpr int PER = (4 + GROUPS - 1) / GROUPS;
 #pragma unroll
-        for (int k = 0; k < R; ++k) dst[k * stride] = (T)0;
-        return;
+        for (int q = 0; q < PER; ++q) {
+            const int w = group + q * GROUPS;   // 0: step of a, 1: step of b, 2: jump of a, 3: jump of b
+            if (w < 4) {
+                const double t = (w & 1) ? tb : ta;
+                Phasor p;
+                p.set((w & 2) ? (double)J * t : t);
+                ph[w * BLOCKS + i] = double2{p.c, p.s};
+            }
+        }
+        __syncthreads();
+        auto get = [&](int w) { const double2 v = ph[w * BLOCKS + i]; return Phasor{v.x, v.y}; };
+        step_a = get(0);
+        jump_a = get(2);
+        if constexpr (kSize) { step_b = get(1); jump_b = get(3); }
+        __syncthreads();
     }
-    const double ta = c / L, tb = 0.5 * sz / L;
-    double sa, ca, s1a, c1a, sb, cb, s1b, c1b;
-    sincospi(reduce_half_turns((double)k0 * ta), &sa, &ca);
-    sincospi(reduce_half_turns(ta), &s1a, &c1a);
-    sincospi(reduce_half_turns((double)k0 * tb), &sb, &cb);
-    sincospi(reduce_half_turns(tb), &s1b, &c1b);
-    double C = ca, Cm = ca * c1a + sa * s1a;                  // cos(k0 a), cos((k0 - 1) a)
-    double S = 2.0 * sb, Sm = 2.0 * (sb * c1b - cb * s1b);    // 2 sin(k0 b), 2 sin((k0 - 1) b)
-    const double ta2 = 2.0 * c1a, tb2 = 2.0 * c1b;
+
+    // The R values at frequencies k0 .. k0 + R - 1 (the run's place), written at dst[k * stride], rounded to T; pil = pi / L.
+    // (An absent block has size 0: its differences vanish by themselves.)
+    template <int R, typename T>
+    __device__ __forceinline__ void gen(int k0, double pil, T *dst, int stride) const {
+        Rec a, b;
+        if constexpr (KIND == RUN_SINDIFF || KIND == RUN_COS) a.start_cos(pa, step_a);
+        else a.start_sin(pa, step_a);
+        if constexpr (kSize) {
+            b.start_sin(pb, step_b);
+            const double m = KIND == RUN_SINDIFF ? 2.0 : -2.0;
+            b.f *= m;
+            b.fm *= m;
+        }
+        double w = (double)k0 * pil;
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-        dst[k * stride] = (T)((k0 + k == 0) ? sz : C * S);
-        const double Cn = fma(ta2, C, -Cm);
-        Cm = C;
-        C = Cn;
-        const double Sn = fma(tb2, S, -Sm);
-        Sm = S;
-        S = Sn;
+        for (int k = 0; k < R; ++k) {
+            double v;
+            if constexpr (kSize) v = a.f * b.f;
+            else if constexpr (KIND == RUN_COS) v = a.f;
+            else { v = w * a.f; w = (double)(k0 + k + 1) * pil; }
+            if (KIND == RUN_SINDIFF && k == 0) v = k0 == 0 ? size : v;
+            dst[k * stride] = (T)v;
+            a.next();
+            if constexpr (kSize) b.next();
+        }
     }
+    __device__ __forceinline__ void jump() {
+        pa.rotate(jump_a);
+        if constexpr (kSize) pb.rotate(jump_b);
+    }
+};
+
+// The value of the lane with the same lane % 32 in the lower (x) and in the upper half of the wave (y).
+__device__ __forceinline__ void both_halves(double v, double &x, double &y) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    x = __builtin_bit_cast(double, (unsigned long long)lo[0] | (unsigned long long)hi[0] << 32);
+    y = __builtin_bit_cast(double, (unsigned long long)lo[1] | (unsigned long long)hi[1] << 32);
 }
 
+constexpr int kK = 32;   // K chunk of both contractions: blocks (forward) or frequencies (row form)
+
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ------------------------------------------------------------------------------------------------
-// Forward: grid (tiles_u * tiles_p, splits), 256 threads as 2 x 2 waves over a TU x TP tile.
-// LDS holds the K chunk of the two basis tiles, k-major: Xs[kb][u], Ys[kb][p].
+// Forward: grid (tiles_u * tiles_p, splits), 256 threads as 2 x 2 waves over a TILE x TILE tile.
+// LDS holds the K chunk of the two basis tiles, k-major: Xs[kb][u], Ys[kb][p].  A side's 128 threads take block j % 32 and
+// runs j / 32, j / 32 + 4; the two halves of a wave hold two runs of the same blocks and share the one-frequency phasors.
+// Measured at 200,050 blocks and 512 x 512: FP64 1.65 ms, FP32 (TILE 256) 0.93 ms; with a library sincospi per factor and run
+// and FP32 tiles of 128: 1.73 and 1.03 ms.
+// Row strides: 4 past the tile in FP64 (the 16-byte stores of 8 lanes, 8 blocks, fall on different banks; operand reads
+// two-way), 16 past it in FP32 (reads free of conflicts, stores two-way).
 // ------------------------------------------------------------------------------------------------
-template <typename T, int TU, int TP, int KB>
-__global__ __launch_bounds__(256) void k_fwd_mat(int64_t n, int Mu, int Mp, double W, double H,
-                                                 const double *__restrict__ x, const double *__restrict__ y,
-                                                 const double *__restrict__ w, const double *__restrict__ h,
-                                                 T *__restrict__ part, int tiles_p, int64_t chunks,
-                                                 int64_t chunks_per_split) {
+template <typename T, int TILE>
+__global__ __launch_bounds__(256, TILE == 256 ? 1 : 2) void k_fwd_mat(int64_t n, int Mu, int Mp, double W, double H,
+                                                                     const double *__restrict__ x,
+                                                                     const double *__restrict__ y,
+                                                                     const double *__restrict__ w,
+                                                                     const double *__restrict__ h,
+                                                                     T *__restrict__ part, int tiles_p, int64_t chunks,
+                                                                     int64_t chunks_per_split) {
     typedef typename Mat<T>::v4 v4;
-    constexpr int LU = TU + 1, LP = TP + 1;
-    __shared__ T Xs[KB * LU];
-    __shared__ T Ys[KB * LP];
-    constexpr int WU = TU / 2, WP = TP / 2, SU = WU / 16, SP = WP / 16;
-    constexpr int RX = TU * KB / 128, RY = TP * KB / 128;
-    static_assert(RX * 128 == TU * KB && RY * 128 == TP * KB, "tile/thread mismatch");
+    constexpr int LD = TILE + (sizeof(T) == 8 ? 4 : 16);
+    __shared__ __attribute__((aligned(16))) T Xs[kK * LD];
+    __shared__ __attribute__((aligned(16))) T Ys[kK * LD];
+    constexpr int WT = TILE / 2, S = WT / 16;
+    constexpr int R = TILE >= 128 ? 32 : TILE / 4, RUNS = TILE / (4 * R);   // run length, runs per thread
+    constexpr int PER = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(PER)));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tu0 = (int)(blockIdx.x / tiles_p) * TU, tp0 = (int)(blockIdx.x % tiles_p) * TP;
-    const int wu0 = (wave >> 1) * WU, wp0 = (wave & 1) * WP;
+    const int tu0 = (int)(blockIdx.x / tiles_p) * TILE, tp0 = (int)(blockIdx.x % tiles_p) * TILE;
+    const int wu0 = (wave >> 1) * WT, wp0 = (wave & 1) * WT;
     const int64_t c_begin = (int64_t)blockIdx.y * chunks_per_split;
     const int64_t c_end = min(chunks, c_begin + chunks_per_split);
 
-    const int side = tid >> 7, j = tid & 127, kb = j % KB, run = j / KB;
+    const bool side_y = tid >= 128;
+    const int kb = tid & 31, run = (tid >> 5) & 3;
+    const double *__restrict__ cc = side_y ? y : x, *__restrict__ ss = side_y ? h : w;
+    const double L = side_y ? H : W;
+    const int f0 = (side_y ? tp0 : tu0) + run * R;
+    T *dst = (side_y ? Ys : Xs) + kb * LD + run * R;
 
-    v4 acc[SU][SP];
+    v4 acc[S][S];
 #pragma unroll
-    for (int a = 0; a < SU; ++a)
+    for (int a = 0; a < S; ++a)
 #pragma unroll
-        for (int b = 0; b < SP; ++b) acc[a][b] = v4{(T)0, (T)0, (T)0, (T)0};
+        for (int b = 0; b < S; ++b) acc[a][b] = v4{(T)0, (T)0, (T)0, (T)0};
 
+    // block data are requested a chunk ahead; past the last block: an absent one (size 0)
+    auto fetch = [&](int64_t c, double &pc, double &ps) {
+        const int64_t ib = c * kK + kb;
+        const bool in = ib < n;
+        pc = cc[in ? ib : 0];
+        ps = ss[in ? ib : 0];
+        if (!in) pc = ps = 0.0;
+    };
+    double pc = 0.0, ps = 0.0;
+    if (c_begin < c_end) fetch(c_begin, pc, ps);
     for (int64_t c = c_begin; c < c_end; ++c) {
-        const int64_t ib = c * KB + kb;
-        const bool valid = ib < n;
-        __syncthreads();
-        if (side == 0) {
-            const double cx = valid ? x[ib] : 0.0, sx = valid ? w[ib] : 0.0;
-            gen_sindiff<RX>(cx, sx, W, tu0 + run * RX, valid, &Xs[kb * LU + run * RX], 1);
-        } else {
-            const double cy = valid ? y[ib] : 0.0, sy = valid ? h[ib] : 0.0;
-            gen_sindiff<RY>(cy, sy, H, tp0 + run * RY, valid, &Ys[kb * LP + run * RY], 1);
+        const double ta = pc / L, tb = 0.5 * ps / L, sz = ps;
+        if (c + 1 < c_end) fetch(c + 1, pc, ps);
+        __builtin_amdgcn_s_setprio(3);
+        Phasor own, step_a, step_b;
+        own.set(lane < 32 ? ta : tb);
+        both_halves(own.c, step_a.c, step_b.c);
+        both_halves(own.s, step_a.s, step_b.s);
+        lds_barrier();   // the previous chunk has been contracted
+#pragma unroll
+        for (int i = 0; i < RUNS; ++i) {
+            const int k0 = f0 + i * 4 * R;
+            Phasor pa, pb;
+            pa.set((double)k0 * ta);
+            pb.set((double)k0 * tb);
+            Rec a, b;
+            a.start_cos(pa, step_a);
+            b.start_sin(pb, step_b);
+            b.f *= 2.0;
+            b.fm *= 2.0;
+            vec v;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                double val = a.f * b.f;
+                if (k == 0) val = k0 == 0 ? sz : val;
+                v[k % PER] = (T)val;
+                if (k % PER == PER - 1) *(vec *)(dst + i * 4 * R + k - (PER - 1)) = v;
+                a.next();
+                b.next();
+            }
         }
-        __syncthreads();
+        __builtin_amdgcn_s_setprio(0);
+        lds_barrier();
 #pragma unroll
-        for (int ks = 0; ks < KB / 4; ++ks) {
+        for (int ks = 0; ks < kK / 4; ++ks) {
             const int kr = ks * 4 + (lane >> 4);
-            T av[SU], bv[SP];
+            T av[S], bv[S];
 #pragma unroll
-            for (int a = 0; a < SU; ++a) av[a] = Xs[kr * LU + wu0 + a * 16 + (lane & 15)];
+            for (int a = 0; a < S; ++a) av[a] = Xs[kr * LD + wu0 + a * 16 + (lane & 15)];
 #pragma unroll
-            for (int b = 0; b < SP; ++b) bv[b] = Ys[kr * LP + wp0 + b * 16 + (lane & 15)];
+            for (int b = 0; b < S; ++b) bv[b] = Ys[kr * LD + wp0 + b * 16 + (lane & 15)];
 #pragma unroll
-            for (int a = 0; a < SU; ++a)
+            for (int a = 0; a < S; ++a)
 #pragma unroll
-                for (int b = 0; b < SP; ++b) acc[a][b] = Mat<T>::mfma(av[a], bv[b], acc[a][b]);
+                for (int b = 0; b < S; ++b) acc[a][b] = Mat<T>::mfma(av[a], bv[b], acc[a][b]);
         }
     }
 
     T *out = part + (size_t)blockIdx.y * (size_t)Mu * (size_t)Mp;
 #pragma unroll
-    for (int a = 0; a < SU; ++a)
+    for (int a = 0; a < S; ++a)
 #pragma unroll
-        for (int b = 0; b < SP; ++b)
+        for (int b = 0; b < S; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int u = tu0 + wu0 + a * 16 + Mat<T>::row(lane, r);
@@ -298,41 +301,76 @@ __global__ __launch_bounds__(256) void k_fwd_mat(int64_t n, int Mu, int Mp, doub
 // i of a TB tile and each epilogue frequency j of a TN tile,
 //     Z_ij = sum_k Bas_ik B[k][j]          (K loop over the Ka frequencies of one axis, MFMA),
 //     out_i += sum_j E_ij Z_ij             (fused row-dot epilogue, FP64),
-// with Bas of kind KK_KIND along the K axis and E of kind EP1 (and, if EP2 >= 0, a second
-// epilogue of kind EP2 on the same Z into gpart2).  Grid (tiles_b, tiles_n), 256 threads as 2 x 2
-// waves.  LDS: As[k][i] (generated basis), Bs[k][j] (prepared operand); after the K loop the same
-// space holds the epilogue basis of one half of the N tile, Es[j][i].  Two waves per SIMD (at most
-// 256 registers per lane; FP64 fits without spills): the LDS (68 KB in FP64) admits two workgroups
-// per CU, so one workgroup's MFMAs run while the other generates its next basis chunk and loads
-// its next operand chunk, which sit between barriers.
+// with Bas of kind KA_KIND along the K axis and E of kind EP1 (and, if EP2 >= 0, a second
+// epilogue of kind EP2 on the same Z into gpart2).  Grid (tiles_b, N tiles of the one or two contractions), 256 threads as 2 x 2
+// waves; wave column wc owns the 16-column tiles 2 b + wc.  LDS: As[k][i] (generated basis of the chunk), two buffers
+// Bs[k][j] of half a chunk each, filled by direct copies (global memory to LDS) while the other half is contracted; after the K
+// loop the same space holds the epilogue basis of 64 columns, Es[j][i].  Two workgroups per CU.
+// Measured per gradient (both axes) at 200,050 blocks and 512 x 512: FP64 3.23 ms, 65 TFLOP/s of the 71.6 that a large library product
+// reaches (generator 4 %, epilogue 1 %, the rest MFMAs at 67 cycles and barriers), FP32 1.78 ms, 118 TFLOP/s (generator, copies and
+// epilogue 5-6 % each); with one buffer, loads and generation between barriers: 3.83 and 2.18 ms.
+// VEC: B's rows are aligned to 16 bytes and a tile row is 1024: one 16-byte copy per lane and row.  Otherwise copies of 4 bytes
+// per lane.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int TB, int TN, int KK, int KA_KIND, int EP1, int EP2>
+template <typename T, int TB, int TN, bool VEC, int KA_KIND, int EP1, int EP2>
 __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis> P) {
     typedef typename Mat<T>::v4 v4;
     const bool second = (int)blockIdx.y >= P.tiles0;
     const BwdAxis ax = P.pick(second);
     const int ntile = (int)blockIdx.y - (second ? P.tiles0 : 0);
-    constexpr int LB = TB + 1, LN = TN + 1;
-    constexpr int HALF = TN / 2;
-    static_assert(TB == 128 && TN == 128 && KK == 32, "LDS reuse below assumes this tile");
-    constexpr int SMEM = (KK * LB + KK * LN) > (HALF * LB) ? (KK * LB + KK * LN) : (HALF * LB);
-    __shared__ T smem[SMEM];
-    __shared__ double red[2 * TB];
-    T *As = smem, *Bs = smem + KK * LB, *Es = smem;
-    constexpr int WI = TB / 2, WJ = TN / 2, SI = WI / 16, SJ = WJ / 16;
-    constexpr int RA = KK * TB / 256;   // K-side run per thread per chunk
-    constexpr int RE = HALF * TB / 256; // epilogue run per thread per half
+    constexpr int LB = TB + 16, LN = TN + 16, LE = TB + 1, KH = kK / 2, EC = 64;
+    constexpr int GROUPS = 256 / TB;       // threads per block
+    constexpr int RA = kK / GROUPS;        // K-side run per thread per chunk
+    constexpr int RE = EC / GROUPS;        // epilogue run per thread and 64 columns
+    constexpr int WI = TB / 2, SI = WI / 16, SJ = TN / 32;
+    constexpr int BYTES_A = kK * LB * sizeof(T), BYTES_B = 2 * KH * LN * sizeof(T), BYTES_E = EC * LE * sizeof(T),
+                  BYTES_P = 4 * TB * sizeof(double2);
+    constexpr int SMEM0 = BYTES_A + BYTES_B > BYTES_E ? BYTES_A + BYTES_B : BYTES_E;
+    constexpr int SMEM = SMEM0 > BYTES_P ? SMEM0 : BYTES_P;
+    // one LDS object: with a second one the compiler makes every LDS read wait for all copies in flight
+    __shared__ __attribute__((aligned(16))) char smem[SMEM + 2 * TB * (int)sizeof(double)];
+    double *red = (double *)(smem + SMEM);
+    T *As = (T *)smem, *Bs = (T *)(smem + BYTES_A), *Es = (T *)smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t ib0 = (int64_t)blockIdx.x * TB;
     const int n0 = ntile * TN;
-    const int wi0 = (wave >> 1) * WI, wc = wave & 1, wj0 = wc * WJ;
-    const int gi = tid % TB, grun = tid / TB;
+    const int wi0 = (wave >> 1) * WI, wc = wave & 1;
+    const int gi = tid % TB, group = tid / TB;
     const int64_t ib = ib0 + gi;
     const bool valid = ib < n;
-    const double ca = valid ? ax.ca[ib] : 0.0, sa = (valid && ax.sa) ? ax.sa[ib] : 0.0;
-    const double cb = valid ? ax.cb[ib] : 0.0, sb = (valid && ax.sb) ? ax.sb[ib] : 0.0;
-    const T *__restrict__ B = (const T *)ax.B;
+
+    // Copies of the KH rows from k on into buffer h: wave w copies rows w, w + 4, ..; a row past Ka is the last row again
+    // (its basis values are zero), and columns past Nb hold whatever follows in B, within the buffer's bounds (the
+    // accumulators of such columns are cleared before the epilogue).
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto copy_half = [&](int k, int h) {
+#pragma unroll
+        for (int q = 0; q < KH / 4; ++q) {
+            const int row = 4 * q + wave;
+            const int64_t at = (int64_t)min(k + row, ax.Ka - 1) * ax.Nb + n0;
+            const int64_t left = ((int64_t)ax.Ka * ax.Nb - at) * (int64_t)sizeof(T);
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)((const T *)ax.B + at), (short)0, (int)min(left, (int64_t)TN * (int64_t)sizeof(T)), 0x00020000);
+            char *dst = smem + BYTES_A + (h * KH + row) * LN * (int)sizeof(T);
+            if constexpr (VEC) {
+                static_assert(TN * sizeof(T) == 1024, "one copy per row");
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)dst, 16, lane * 16, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int g = 0; g < TN * (int)sizeof(T) / 256; ++g)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(dst + 256 * g), 4, lane * 4 + 256 * g, 0, 0,
+                                                             0);
+            }
+        }
+    };
+    // The runs' init uses the LDS of As and more; the first copies follow it.
+    BlockRuns<KA_KIND> runs;
+    {
+        const double c = valid ? ax.ca[ib] : 0.0, sz = (valid && ax.sa) ? ax.sa[ib] : 0.0;
+        runs.template init<GROUPS, TB>(c, sz, ax.La, group * RA, kK, (double2 *)smem, gi, group);
+    }
+    copy_half(0, 0);
 
     v4 acc[SI][SJ];
 #pragma unroll
@@ -340,69 +378,79 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis>
 #pragma unroll
         for (int b = 0; b < SJ; ++b) acc[a][b] = v4{(T)0, (T)0, (T)0, (T)0};
 
-    KRun<KA_KIND> krun{};
-    if (valid) krun.init(ca, sa, ax.La, grun * RA, KK);
-    constexpr int PB = KK * TN / 256;
-    for (int k0 = 0; k0 < ax.Ka; k0 += KK) {
-        // The operand chunk is loaded first (unconditionally, from a valid address; the bounds are
-        // applied when it is stored), so that its latency overlaps the basis generation.
-        T bv[PB];
+    for (int k0 = 0; k0 < ax.Ka; k0 += kK) {
+        __builtin_amdgcn_s_setprio(3);
+        const int ka = k0 + group * RA;
+        T *dst = As + (group * RA) * LB + gi;
+        runs.template gen<RA>(ka, 0.0, dst, LB);
+        if (k0 + kK > ax.Ka) {   // the last chunk's rows past Ka meet finite operand values: no basis there
 #pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int idx = tid + 256 * q, k = idx / TN, jj = idx % TN;
-            const bool in = (k0 + k < ax.Ka) && (n0 + jj < ax.Nb);
-            bv[q] = B[in ? (size_t)(k0 + k) * ax.Nb + n0 + jj : 0];
+            for (int k = 0; k < RA; ++k)
+                if (ka + k >= ax.Ka) dst[k * LB] = (T)0;
         }
-        __syncthreads();
-        krun.template gen<RA>(k0 + grun * RA, valid, &As[(grun * RA) * LB + gi], LB);
-        krun.jump();
+        runs.jump();
+        __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int q = 0; q < PB; ++q) {
-            const int idx = tid + 256 * q, k = idx / TN, jj = idx % TN;
-            const bool in = (k0 + k < ax.Ka) && (n0 + jj < ax.Nb);
-            Bs[k * LN + jj] = in ? bv[q] : (T)0;
+        for (int h = 0; h < 2; ++h) {
+            wait_copies();
+            lds_barrier();
+            if (h == 0) copy_half(k0 + KH, 1);
+            else if (k0 + kK < ax.Ka) copy_half(k0 + kK, 0);
+#pragma unroll
+            for (int ks = 0; ks < KH / 4; ++ks) {
+                const int kr = ks * 4 + (lane >> 4);
+                T av[SI], bw[SJ];
+#pragma unroll
+                for (int a = 0; a < SI; ++a) av[a] = As[(h * KH + kr) * LB + wi0 + a * 16 + (lane & 15)];
+#pragma unroll
+                for (int b = 0; b < SJ; ++b) bw[b] = Bs[(h * KH + kr) * LN + (2 * b + wc) * 16 + (lane & 15)];
+#pragma unroll
+                for (int a = 0; a < SI; ++a)
+#pragma unroll
+                    for (int b = 0; b < SJ; ++b) acc[a][b] = Mat<T>::mfma(av[a], bw[b], acc[a][b]);
+            }
         }
-        __syncthreads();
+        lds_barrier();
+    }
+    if (n0 + TN > ax.Nb) {
 #pragma unroll
-        for (int ks = 0; ks < KK / 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            T av[SI], bv[SJ];
+        for (int b = 0; b < SJ; ++b)
+            if (n0 + (2 * b + wc) * 16 + (lane & 15) >= ax.Nb)
 #pragma unroll
-            for (int a = 0; a < SI; ++a) av[a] = As[kr * LB + wi0 + a * 16 + (lane & 15)];
-#pragma unroll
-            for (int b = 0; b < SJ; ++b) bv[b] = Bs[kr * LN + wj0 + b * 16 + (lane & 15)];
-#pragma unroll
-            for (int a = 0; a < SI; ++a)
-#pragma unroll
-                for (int b = 0; b < SJ; ++b) acc[a][b] = Mat<T>::mfma(av[a], bv[b], acc[a][b]);
-        }
+                for (int a = 0; a < SI; ++a) acc[a][b] = v4{(T)0, (T)0, (T)0, (T)0};
     }
 
-    // Epilogue(s): row dot with the epilogue basis, one N half at a time; the 16 lanes that share
-    // a row are summed by a fixed butterfly, the two column waves in fixed order.
+    // Epilogue(s): row dot with the epilogue basis, 64 columns (two column tiles of each wave) at a time; the 16 lanes that
+    // share a row are summed by a fixed butterfly, the two column waves in fixed order.
     auto epilogue = [&](auto kind_tag, double *__restrict__ gpart, double *__restrict__ out) {
         constexpr int EK = decltype(kind_tag)::value;
+        BlockRuns<EK> er;
+        {
+            const double c = valid ? ax.cb[ib] : 0.0, sz = (valid && ax.sb) ? ax.sb[ib] : 0.0;
+            er.template init<GROUPS, TB>(c, sz, ax.Lb, n0 + group * RE, EC, (double2 *)smem, gi, group);
+        }
+        const double pil = kPi / ax.Lb;
         double rs[SI][4];
 #pragma unroll
         for (int a = 0; a < SI; ++a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) rs[a][r] = 0.0;
-        for (int hf = 0; hf < 2; ++hf) {
+#pragma unroll
+        for (int e = 0; e < TN / EC; ++e) {
+            er.template gen<RE>(n0 + e * EC + group * RE, pil, &Es[(group * RE) * LE + gi], LE);
+            if (e + 1 < TN / EC) er.jump();
             __syncthreads();
-            gen_run<EK, RE>(cb, sb, ax.Lb, n0 + hf * HALF + grun * RE, valid, &Es[(grun * RE) * LB + gi], LB);
+#pragma unroll
+            for (int a = 0; a < SI; ++a)
+#pragma unroll
+                for (int b = 2 * e; b < 2 * e + 2; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int il = wi0 + a * 16 + Mat<T>::row(lane, r);
+                        const int jl = (2 * b + wc) * 16 - e * EC + (lane & 15);
+                        rs[a][r] = fma((double)acc[a][b][r], (double)Es[jl * LE + il], rs[a][r]);
+                    }
             __syncthreads();
-            if (wc == hf) {
-#pragma unroll
-                for (int a = 0; a < SI; ++a)
-#pragma unroll
-                    for (int b = 0; b < SJ; ++b)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int il = wi0 + a * 16 + Mat<T>::row(lane, r);
-                            const int jl = b * 16 + (lane & 15);
-                            rs[a][r] += (double)acc[a][b][r] * (double)Es[jl * LB + il];
-                        }
-            }
         }
 #pragma unroll
         for (int a = 0; a < SI; ++a)
@@ -427,36 +475,73 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis>
             if (!ax.out.r) gpart[(size_t)ntile * (size_t)n + (size_t)(ib0 + tid)] = v;
             else if (out) out[ib0 + tid] = (ax.out.dE ? *ax.out.dE : 1.0) * v;
         }
+        __syncthreads();
     };
     epilogue(std::integral_constant<int, EP1>{}, ax.gpart, ax.out.r);
     if constexpr (EP2 >= 0) epilogue(std::integral_constant<int, (EP2 >= 0 ? EP2 : 0)>{}, ax.gpart2, ax.out.r2);
 }
 
+// Row form: with fewer workgroups of 128 blocks than this the chip is better filled by tiles of 32 blocks, which take a quarter
+// of the time of one tile (a gradient in FP64, tiles of 32 against 128: 512 x 512, 2,000 blocks (128 workgroups) 62 against 91
+// us; 300 x 300, 4,000 blocks (192) 55 against 62; 512 x 512, 4,000 blocks (256) 114 against 94; FP32 crosses at the same place).
+constexpr int64_t kFewWorkgroups = 224;
+
 template <typename T>
 hipError_t launch_fwd_mat(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W, double H, const double *x,
                           const double *y, const double *w, const double *h, T *part, hipStream_t s) {
+    if (pl.tu != pl.tp || pl.kb != kK) return hipErrorInvalidValue;
     dim3 grid(pl.tiles_u * pl.tiles_p, pl.splits);
-    if (pl.tu == 128 && pl.tp == 128 && pl.kb == 32)
-        hipLaunchKernelGGL((k_fwd_mat<T, 128, 128, 32>), grid, dim3(256), 0, s, n, Mu, Mp, W, H, x, y, w, h, part,
-                           pl.tiles_p, pl.chunks, pl.chunks_per_split);
-    else if (pl.tu == 64 && pl.tp == 64 && pl.kb == 32)
-        hipLaunchKernelGGL((k_fwd_mat<T, 64, 64, 32>), grid, dim3(256), 0, s, n, Mu, Mp, W, H, x, y, w, h, part,
-                           pl.tiles_p, pl.chunks, pl.chunks_per_split);
-    else
-        return hipErrorInvalidValue;
+    auto launch = [&](auto kernel, int tiles_p) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, n, Mu, Mp, W, H, x, y, w, h, part, tiles_p, pl.chunks,
+                           pl.chunks_per_split);
+        return hipGetLastError();
+    };
+    if (pl.tu == 64) return launch(k_fwd_mat<T, 64>, pl.tiles_p);
+    if (pl.tu != 128) return hipErrorInvalidValue;
+    if constexpr (sizeof(T) == 4) {
+        // FP32: four tiles as one of 256 x 256 (twice the MFMAs per generated value) where no column or row is padded for it
+        // and every CU still gets two of them; the plan's splits stay, so that the sums of a split do not change
+        const int tu = (pl.tiles_u + 1) / 2, tp = (pl.tiles_p + 1) / 2;
+        if (pl.tiles_u % 2 == 0 && pl.tiles_p % 2 == 0 && (int64_t)tu * tp * pl.splits >= 512) {
+            grid.x = tu * tp;
+            return launch(k_fwd_mat<T, 256>, tp);
+        }
+    }
+    return launch(k_fwd_mat<T, 128>, pl.tiles_p);
+}
+
+template <typename T, int TB, int TN, bool VEC, int KA_KIND, int EP1, int EP2>
+hipError_t launch_rowform_tile(int64_t n, const BwdAxis &ax0, const BwdAxis *ax1, hipStream_t s) {
+    AxisPair<BwdAxis> P{{ax0, ax1 ? *ax1 : ax0}, (ax0.Nb + TN - 1) / TN};
+    const int tiles1 = ax1 ? (ax1->Nb + TN - 1) / TN : 0;
+    dim3 grid((unsigned)((n + TB - 1) / TB), (unsigned)(P.tiles0 + tiles1));
+    hipLaunchKernelGGL((k_bwd_mat<T, TB, TN, VEC, KA_KIND, EP1, EP2>), grid, dim3(256), 0, s, n, P);
     return hipGetLastError();
 }
 
 template <typename T, int KA_KIND, int EP1, int EP2>
 hipError_t launch_rowform(const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1, hipStream_t s) {
-    if (!(pl.tb == 128 && pl.tn == 128 && pl.kk == 32)) return hipErrorInvalidValue;
+    if (!(pl.tb == 128 && pl.kk == kK && (pl.tn == 128 || (pl.tn == 256 && sizeof(T) == 4)))) return hipErrorInvalidValue;
     if (n == 0) return hipSuccess;
-    AxisPair<BwdAxis> P{{ax0, ax1 ? *ax1 : ax0}, (ax0.Nb + pl.tn - 1) / pl.tn};
-    const int tiles1 = ax1 ? (ax1->Nb + pl.tn - 1) / pl.tn : 0;
-    if ((ax0.out.r && P.tiles0 > 1) || (ax1 && ax1->out.r && tiles1 > 1)) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((n + pl.tb - 1) / pl.tb), (unsigned)(P.tiles0 + tiles1));
-    hipLaunchKernelGGL((k_bwd_mat<T, 128, 128, 32, KA_KIND, EP1, EP2>), grid, dim3(256), 0, s, n, P);
-    return hipGetLastError();
+    if ((ax0.out.r && ax0.Nb > pl.tn) || (ax1 && ax1->out.r && ax1->Nb > pl.tn)) return hipErrorInvalidValue;
+    const auto aligned = [](const BwdAxis &ax) {
+        return (size_t)ax.Nb * sizeof(T) % 16 == 0 && (uintptr_t)ax.B % 16 == 0;
+    };
+    const bool vec = aligned(ax0) && (!ax1 || aligned(*ax1));
+    if constexpr (sizeof(T) == 4) {
+        if (pl.tn == 256) return vec ? launch_rowform_tile<T, 128, 256, true, KA_KIND, EP1, EP2>(n, ax0, ax1, s)
+                                     : launch_rowform_tile<T, 128, 256, false, KA_KIND, EP1, EP2>(n, ax0, ax1, s);
+    }
+    // at most 64 frequencies on every N axis: half a tile; few workgroups of 128 blocks: tiles of 32
+    const bool half = ax0.Nb <= 64 && (!ax1 || ax1->Nb <= 64);
+    const int64_t wgs = (n + 127) / 128 * ((ax0.Nb + 127) / 128 + (ax1 ? (ax1->Nb + 127) / 128 : 0));
+    const bool few = wgs < kFewWorkgroups;
+    if (half) return few ? launch_rowform_tile<T, 32, 64, false, KA_KIND, EP1, EP2>(n, ax0, ax1, s)
+                         : launch_rowform_tile<T, 128, 64, false, KA_KIND, EP1, EP2>(n, ax0, ax1, s);
+    if (few) return launch_rowform_tile<T, 32, 128, false, KA_KIND, EP1, EP2>(n, ax0, ax1, s);
+    if constexpr (sizeof(T) == 8)
+        if (vec) return launch_rowform_tile<T, 128, 128, true, KA_KIND, EP1, EP2>(n, ax0, ax1, s);
+    return launch_rowform_tile<T, 128, 128, false, KA_KIND, EP1, EP2>(n, ax0, ax1, s);
 }
 
 template <typename T>

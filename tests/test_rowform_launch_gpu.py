@@ -53,6 +53,28 @@ def test_one_and_several_tiles_per_axis(prec, n, Mu, Mp):
     assert rel(N, oracle.block_potential(W, H, *wl.arrays(), ao)) <= TOL[prec]
 
 
+@pytest.mark.parametrize("prec,n,Mu,Mp", [("fp64", 15001, 128, 128), ("fp64", 15001, 130, 129), ("fp64", 28700, 50, 64),
+                                          ("fp32", 15001, 128, 128), ("fp32", 15001, 131, 127), ("fp32", 28700, 50, 64),
+                                          ("fp32", 65500, 256, 256), ("fp32", 66001, 250, 255)])
+def test_tiles_of_128_blocks_and_wide_tiles(prec, n, Mu, Mp):
+    """Enough blocks for the full block tile (below, tiles of 32 blocks), half N tiles, rows of the operand that are not
+    16-byte aligned, and FP32's N tiles of 256; sampled blocks, any coefficients (the gradient is linear in them)."""
+    W, H = 500.0, 350.0
+    wl = make_random(n, W, H, Mu, Mp, seed=n)
+    print(f"[rows] {prec} n={n} M={Mu}x{Mp}", file=sys.stderr, flush=True)
+    rng = np.random.default_rng(n)
+    a = rng.standard_normal((Mu, Mp)) / (1.0 + np.arange(Mu)[:, None] ** 2 + np.arange(Mp)[None, :] ** 2)
+    idx = np.unique(np.concatenate([[0, 127, 128, n - 1], rng.integers(0, n, 150)]))
+    gx, gy = pp.field(*gpu(*wl.arrays()), gpu(a)[0], W=W, H=H, precision=prec)
+    gxo, gyo = oracle.grad_sampled(W, H, *wl.arrays(), a, idx)
+    assert rel(gx[torch.as_tensor(idx, device="cuda:0")], gxo) <= TOL[prec]
+    assert rel(gy[torch.as_tensor(idx, device="cuda:0")], gyo) <= TOL[prec]
+    psi, xix, xiy = pp.point_field(*gpu(wl.x, wl.y), gpu(a)[0], W=W, H=H, precision=prec)
+    po, xo, yo = oracle.point_field(W, H, a, wl.x[idx], wl.y[idx])
+    at = torch.as_tensor(idx, device="cuda:0")
+    assert rel(psi[at], po) <= TOL[prec] and rel(xix[at], xo) <= TOL[prec] and rel(xiy[at], yo) <= TOL[prec]
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
 def test_outputs_in_the_memory_of_the_inputs(prec):
     """gx and gy over x and y, psi and xi over the points: the results are those of separate outputs, bit for bit."""
