@@ -6,10 +6,8 @@
 namespace pp {
 namespace {
 
-constexpr int kRedThreads = 256;   // coefficients per block of the split-K reduction
-constexpr int kRedGroups = 4;      // threads per coefficient
-constexpr int kRedBatch = 32;       // splits per batch
-constexpr int kRedMaxBlocks = 1 << 20;   // a grid stays below 2^32 work-items
+constexpr int kRedCoefs = 256;   // coefficients of a block of the split-K reduction: one wave, four a lane
+constexpr int kRedBytes = 256;   // its bytes in flight per lane
 
 // Deterministic block sum of one double per thread (butterfly inside waves, then wave order).
 __device__ __forceinline__ double block_sum(double v, double *scratch) {
@@ -30,63 +28,64 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 // (the four coefficient cases of Sec. III-A written with one scale; a_00 = 0 is the
 // compatibility condition).  The energy partial of this block is sum a_up A_up.
 //
-// Bound by reading the partials.  A block takes 256 coefficients with kRedGroups threads each, in batches of
-// kRedBatch splits: every thread has eight loads in flight, the batch meets in LDS, and the first group adds it in the order of
-// the splits while the next batch is loaded.  The order is the one of a plain sum, so that neither the number of threads nor
-// a change of it shows in a result (an e4m3 operand of the FP8 gradient turns the last bit of a coefficient into 2^-8 of it).
-// (One thread per coefficient with its loads in a chain reached 2.0 TB/s on 481 splits of 512 x 512 (249 us, now 131:
-// 3.9 TB/s) and was latency at 157 splits of 257 x 513 (45 us, now 22).)
+// Bound by reading the partials: a wave takes 256 coefficients, four per lane in vector loads, and keeps kRedBytes per lane
+// (16 splits of FP32 partials) in flight, each load issued as soon as the value in its place is added.  No part of it waits
+// for another wave.  The order is the one of a plain sum over the splits, so that the number in flight does not show in a
+// result (the scale of the FP8 gradient's operands turns the last bit of a coefficient into 1e-8 of the gradient).
+// 481 splits of 512 x 512 (504 MB): 111 us, 4.5 TB/s; 157 splits of 257 x 513: 17.5 us; 5 of 2048 x 2048: 110 us.
+// (One load in a chain per coefficient took 249, 45 and 161 us; four groups of 256 threads that meet in LDS 127, 22 and 144;
+// twice the bytes in flight 120 at 481 splits and the same elsewhere.)
 template <typename T>
-__global__ __launch_bounds__(kRedThreads * kRedGroups) void k_reduce_scale(const T *__restrict__ part, int splits, int Mu,
-                                                                           int Mp, double W, double H,
-                                                                           double *__restrict__ a,
-                                                                           double *__restrict__ epart, int nb) {
-    __shared__ T buf[kRedBatch][kRedThreads];
-    __shared__ double scratch[kRedThreads * kRedGroups / 64];
-    constexpr int PER = kRedBatch / kRedGroups;
+__global__ __launch_bounds__(64) void k_reduce_scale(const T *__restrict__ part, int splits, int Mu, int Mp, double W,
+                                                     double H, double *__restrict__ a, double *__restrict__ epart) {
+    constexpr int D = kRedBytes / (4 * sizeof(T));
+    // A split's plane may begin at any element.
+    typedef T Vec __attribute__((ext_vector_type(4), aligned(sizeof(T))));
     const size_t MM = (size_t)Mu * (size_t)Mp;
-    const int t = threadIdx.x % kRedThreads, g = threadIdx.x / kRedThreads;
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const size_t idx = (size_t)b * kRedThreads + t;
-        const T *__restrict__ p = part + (idx < MM ? idx : 0);
-        double At = 0.0;
-        T v[PER];
-        auto fetch = [&](int s0) {   // splits s0 + PER g ..; past the last one the last again, which is not added
+    const size_t idx = (size_t)blockIdx.x * kRedCoefs + 4 * threadIdx.x;
+    // where fewer than four coefficients are left, the plane's last four
+    const size_t at = MM < 4 ? 0 : min(idx, MM - 4);
+    double At[4] = {};
+    if (MM >= 4) {
+        const T *__restrict__ p = part + at;
+        Vec v[D];
 #pragma unroll
-            for (int k = 0; k < PER; ++k) v[k] = p[(size_t)min(s0 + PER * g + k, splits - 1) * MM];
-        };
-        fetch(0);
-        for (int s0 = 0; s0 < splits; s0 += kRedBatch) {
+        for (int k = 0; k < D; ++k) v[k] = *(const Vec *)(p + (size_t)min(k, splits - 1) * MM);
+        int s = 0;
+        for (; s + D < splits; s += D)
 #pragma unroll
-            for (int k = 0; k < PER; ++k) buf[PER * g + k][t] = v[k];
-            __syncthreads();
-            if (s0 + kRedBatch < splits) fetch(s0 + kRedBatch);
-            if (g == 0) {
-                if (s0 + kRedBatch <= splits) {
+            for (int k = 0; k < D; ++k) {
 #pragma unroll
-                    for (int k = 0; k < kRedBatch; ++k) At += (double)buf[k][t];
-                } else {
-                    for (int k = 0; k < splits - s0; ++k) At += (double)buf[k][t];
-                }
+                for (int c = 0; c < 4; ++c) At[c] += (double)v[k][c];
+                v[k] = *(const Vec *)(p + (size_t)min(s + D + k, splits - 1) * MM);
             }
-            __syncthreads();
-        }
-        double e = 0.0;
-        if (g == 0 && idx < MM) {
-            const int u = (int)(idx / (size_t)Mp), p = (int)(idx % (size_t)Mp);
-            const double wu = (double)u * kPi / W, vp = (double)p * kPi / H;
-            const double wt = u ? wu : 1.0, vt = p ? vp : 1.0;
-            const double A = At / (wt * vt);
-            const double eps = (u ? 2.0 : 1.0) * (p ? 2.0 : 1.0);
-            const double sc = (u == 0 && p == 0) ? 0.0 : eps / (W * H * (wu * wu + vp * vp));
-            const double av = sc * A;
-            if (a) a[idx] = av;
-            e = av * A;
-        }
-        const double sum = block_sum(e, scratch);
-        if (threadIdx.x == 0) epart[b] = sum;
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < D; ++k)
+            if (s + k < splits)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) At[c] += (double)v[k][c];
+    } else {
+        for (int s = 0; s < splits; ++s)
+            for (int c = 0; c < (int)MM; ++c) At[c] += (double)part[(size_t)s * MM + c];
     }
+    double e = 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const size_t id = at + c;
+        if (id < idx || id >= MM) continue;   // another lane's, or none
+        const int u = (int)(id / (size_t)Mp), q = (int)(id % (size_t)Mp);
+        const double wu = (double)u * kPi / W, vp = (double)q * kPi / H;
+        const double wt = u ? wu : 1.0, vt = q ? vp : 1.0;
+        const double A = At[c] / (wt * vt);
+        const double eps = (u ? 2.0 : 1.0) * (q ? 2.0 : 1.0);
+        const double sc = (u == 0 && q == 0) ? 0.0 : eps / (W * H * (wu * wu + vp * vp));
+        const double av = sc * A;
+        if (a) a[id] = av;
+        e += av * A;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) e += __shfl_xor(e, off);
+    if (threadIdx.x == 0) epart[blockIdx.x] = e;
 }
 
 constexpr int kEnergyThreads = 1024;
@@ -151,19 +150,18 @@ __global__ void k_bwd_final(const double *__restrict__ gpx, int tx, const double
 
 int reduce_scale_blocks(int Mu, int Mp) {
     const size_t MM = (size_t)Mu * (size_t)Mp;
-    return (int)((MM + kRedThreads - 1) / kRedThreads);
+    return (int)((MM + kRedCoefs - 1) / kRedCoefs);
 }
 
 hipError_t launch_reduce_scale(const void *part, bool part_f32, int splits, int Mu, int Mp, double W, double H,
                                double *a, double *epart, int *nblocks_out, hipStream_t s) {
     const int nb = reduce_scale_blocks(Mu, Mp);
-    const int grid = nb < kRedMaxBlocks ? nb : kRedMaxBlocks;
     if (part_f32)
-        hipLaunchKernelGGL(k_reduce_scale<float>, dim3(grid), dim3(kRedThreads * kRedGroups), 0, s, (const float *)part,
-                           splits, Mu, Mp, W, H, a, epart, nb);
+        hipLaunchKernelGGL(k_reduce_scale<float>, dim3(nb), dim3(64), 0, s, (const float *)part, splits, Mu, Mp, W, H, a,
+                           epart);
     else
-        hipLaunchKernelGGL(k_reduce_scale<double>, dim3(grid), dim3(kRedThreads * kRedGroups), 0, s, (const double *)part,
-                           splits, Mu, Mp, W, H, a, epart, nb);
+        hipLaunchKernelGGL(k_reduce_scale<double>, dim3(nb), dim3(64), 0, s, (const double *)part, splits, Mu, Mp, W, H, a,
+                           epart);
     if (nblocks_out) *nblocks_out = nb;
     return hipGetLastError();
 }

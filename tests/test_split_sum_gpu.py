@@ -1,6 +1,6 @@
 """The split-K reduction of the coefficient contraction, through pp.energy in FP64 and FP32, at the split counts where its
-loops change (fewer splits than the four thread groups, one and several batches of eight loads per group, remainders) and
-at coefficient counts around its blocks of 256.  Up to 2048 splits a split is one chunk of 32 blocks here, so n = 32 s - r
+loops change (fewer splits than the 16 FP32 or 8 FP64 loads in flight, one and several batches of them, remainders), at
+coefficient counts around its blocks of 256 and where its four coefficients a lane leave a rest.  Up to 2048 splits a split is one chunk of 32 blocks here, so n = 32 s - r
 gives s splits.
 
 Bar: the FP64 oracle; n eps = 1e-11 relative in the worst case at n = 65,000 in FP64, 1e-5 in FP32 (the FP32 path's own bar)."""
@@ -20,7 +20,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("prec,tol", [("fp64", 1e-11), ("fp32", 1e-5)])
 @pytest.mark.parametrize("splits,r,Mu,Mp", [(1, 31, 1, 1), (2, 0, 16, 16), (3, 5, 17, 15), (4, 0, 64, 64), (28, 1, 5, 7),
-                                            (29, 0, 16, 17), (31, 2, 3, 85), (32, 0, 8, 32), (33, 0, 9, 57), (67, 7, 6, 6),
+                                            (7, 4, 1, 3), (8, 0, 2, 2), (9, 9, 37, 7), (15, 1, 3, 3), (16, 0, 51, 5),
+                                            (17, 8, 257, 1), (29, 0, 16, 17), (31, 2, 3, 85), (32, 0, 8, 32), (33, 0, 9, 57), (67, 7, 6, 6),
                                             (2031, 3, 4, 5)])
 def test_split_counts_and_block_edges(splits, r, Mu, Mp, prec, tol):
     wl = make_random(32 * splits - r, 90.0, 70.0, Mu, Mp, seed=splits)
