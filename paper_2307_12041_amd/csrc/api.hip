@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <initializer_list>
 #include <mutex>
 
@@ -70,6 +71,34 @@ int validate_blocks(const pp_problem *P, const double *x, const double *y, const
     return PP_OK;
 }
 
+// The bf16 forwards from generated bases add the splits on the way (k_fwd_sum_bf16) where that is estimated faster than
+// writing every split's partials and reducing them.  The figures of the estimate, fitted to both routes timed over n = 100 ..
+// 1,000,000 and 40 .. 3000 frequencies per axis: a chunk of a 128 x 128 tile takes 0.92 us (one product: 0.53), a chunk of
+// a 256 x 256 tile 2.45 (1.15); a workgroup begins and ends in 4.5 and 2.7 us, the last stores of the latter take 5; a byte
+// of partials is written and read at 2.7 TB/s together; 256 workgroups run at a time.  (512 x 512 in bf16x3, both stages: n = 10,000 137 us partials, 50 summed;
+// 100,000 314 and 200; 200,000 470 and 376; 400,000 713 and 766.  One product: 130 and 43; 263 and 139; 350 and 254; 494 and 469.)
+// The sums of groups of splits take at most half the splits' partials in bytes, so they fit where those lie.
+void plan_split_sums(const pp_problem &P, FwdPlan &pl) {
+    const bool x3 = P.precision == PP_BF16X3;
+    const double c128 = x3 ? 0.92 : 0.53, c256 = x3 ? 2.45 : 1.15, per_byte = 1.0 / 2.7e6, cps = (double)pl.chunks_per_split;
+    const double MM = (double)P.Mu * (double)P.Mp;
+    const int64_t tiles256 = (int64_t)pl.tiles_u * pl.tiles_p;
+    double best = (double)((tiles256 * pl.splits + 255) / 256) * (cps * c256 + 2.7) + 5.0 +
+                  (double)pl.splits * MM * 4.0 * per_byte;
+    const int64_t tiles = (int64_t)((P.Mu + 127) / 128) * ((P.Mp + 127) / 128);
+    for (const int64_t wgs : {256, 512}) {   // one round of workgroups, or two
+        const int64_t g = std::max<int64_t>(1, std::min<int64_t>(pl.splits / 2, wgs / tiles));
+        const int64_t per = (pl.splits + g - 1) / g, groups = (pl.splits + per - 1) / per;
+        const double us = (double)((tiles * groups + 255) / 256) * ((double)per * cps * c128 + 4.5) +
+                          (double)groups * MM * 8.0 * per_byte;
+        if (us < best) {
+            best = us;
+            pl.groups = (int)groups;
+            pl.splits_per_group = per;
+        }
+    }
+}
+
 FwdPlan fwd_plan(const pp_problem &P) {
     FwdPlan pl{};
     if (is_bf16(P.precision)) {
@@ -103,6 +132,8 @@ FwdPlan fwd_plan(const pp_problem &P) {
     pl.splits = (int)((pl.chunks + pl.chunks_per_split - 1) / pl.chunks_per_split);
     if (pl.splits < 1) pl.splits = 1;
     pl.part_elem = P.precision == PP_FP64 ? 8 : 4;
+    if ((P.precision == PP_BF16X3 || P.precision == PP_BF16) && P.basis_mode != PP_BASIS_STORE && pl.splits >= 2)
+        plan_split_sums(P, pl);
     return pl;
 }
 
@@ -292,6 +323,9 @@ int run_forward(const pp_problem &P, const double *x, const double *y, const dou
             TimedLaunch t(T("fwd"), s);
             err = launch_fwd_bf16_mix(f, mix_tiles(P.Mu), mix_tiles(P.Mp), P.n, P.Mu, P.Mp, tx, ty, sx, sy,
                                       (float *)part, s);
+        } else if (f.groups) {
+            TimedLaunch t(T("fwd"), s);
+            err = launch_fwd_sum_bf16(f, x3, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (double *)part, s);
         } else {
             TimedLaunch t(T("fwd"), s);
             err = launch_fwd_bf16(f, x3, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (float *)part, s);
@@ -305,7 +339,7 @@ int run_forward(const pp_problem &P, const double *x, const double *y, const dou
     }
     if (err != hipSuccess) return PP_ERR_DEVICE;
     int nb = 0;
-    { TimedLaunch t(T("reduce"), s); err = launch_reduce_scale(part, f.part_elem == 4, f.splits, P.Mu, P.Mp, P.W, P.H, a, epart, &nb, s); }
+    { TimedLaunch t(T("reduce"), s); err = launch_reduce_scale(part, f.part_elem == 4 && !f.groups, f.groups ? f.groups : f.splits, P.Mu, P.Mp, P.W, P.H, a, epart, &nb, s); }
     if (err != hipSuccess) return PP_ERR_DEVICE;
     if (E) {
         { TimedLaunch t(T("energy"), s); err = launch_energy_final(epart, nb, E, s); }

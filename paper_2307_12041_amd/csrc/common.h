@@ -27,6 +27,8 @@ struct FwdPlan {
     int64_t chunks;      // ceil(n / kb)
     int64_t chunks_per_split;
     size_t part_elem;    // bytes per partial element (8: FP64, 4: FP32)
+    int groups;          // FP64 sums of splits_per_group splits each in place of the splits' own partials; 0: none
+    int64_t splits_per_group;
 };
 
 struct BwdPlan {
@@ -232,6 +234,8 @@ hipError_t launch_fwd_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp
                            const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
 // Mixed split: the rx x ry low-frequency tiles with k_fwd1_bf16 (three products), the others with
 // the one-product kernel; same partials and plan as launch_fwd_bf16.
+hipError_t launch_fwd_sum_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
+                               const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, double *part, hipStream_t s);
 hipError_t launch_fwd_bf16_mix(const FwdPlan &pl, int rx, int ry, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                                const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
 size_t bwd_bf16_operand_elems(int Np, int Kh);   // bf16 elements of one tiled backward operand

@@ -744,6 +744,282 @@ __global__ __launch_bounds__(256) void k_fwd1_bf16(int64_t n, int Mu, int Mp, co
             }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Forward with the splits added on the way: a workgroup contracts a run of whole splits for one 128 x 128 tile,
+// keeps the FP64 sum over its splits beside the FP32 accumulators of the current one and writes that sum alone.
+// The FP32 sums of a split are those of k_fwd1_bf16 to the bit (same products, same order).
+//
+// Where a split is short, k_fwd1_bf16 is bound by its partials: a 256 KB tile written per split (5.5-9 us of a workgroup's
+// 11-47 us) and read back by the reduction.  Here none of them leaves the registers; the price is twice the generated
+// runs per product, as the tile is half as wide (FP64 sums of a 256-wide tile would not fit the registers).
+// 256 threads of the 512 generate, 256 contract (waves w and w + 4 share a SIMD): what bounds it is the vector instructions
+// of the generating wave, 182 per chunk beside 24 MFMAs, at 1650 cycles a chunk of which 768 are MFMA.  Measured at n = 200,050,
+// 512 x 512 (13 chunks a split), forward and reduction: 361 + 112 us -> 401 + 9; n = 5,000, 257 x 513 (one chunk a
+// split): 47 + 17 -> 21 + 6 us.  Slower there: all eight waves generating and contracting (405 and 24 us), the same with
+// both interleaved slot by slot (418, 23), four waves interleaved (487, 25), one barrier a chunk (440, 23).
+// ------------------------------------------------------------------------------------------------
+constexpr int GT = 128;                  // output tile (u and p)
+constexpr int GROW = GT * 2;             // bytes per LDS row
+constexpr int GARR = FKB * GROW;         // bytes per array
+constexpr int GCHUNK = 4 * GARR;         // Xh, Xl, Yh, Yl of a chunk
+constexpr int GRING = 4;                 // chunks in LDS
+
+__device__ __forceinline__ int gswz(int k, int seg) { return k * GROW + ((seg ^ fswz_mask(k)) << 4); }
+
+// Run r of block k of a pair of chunks, split and stored into arr (the lo halves GARR further) and one chunk
+// further.  The two runs are independent chains: one alone would wait for the latency of its recurrences.
+template <bool X3>
+__device__ __forceinline__ void sum_gen(const GenRec &R0, const GenRec &R1, int u0, char *arr, int k, int r) {
+    Cheb ca[2], sb[2];
+    start_run(R0, ca[0], sb[0]);
+    start_run(R1, ca[1], sb[1]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        float v[2][8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (m == 0 && j == 0) {
+                    v[t][0] = ca[t].f * sb[t].f;
+                    if (u0 == 0) v[t][0] = t ? R1.size : R0.size;
+                } else {
+                    v[t][j] = ca[t].next1() * sb[t].next1();
+                }
+            }
+        unsigned h[2][4], l[2][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                h[t][e] = pack_bf16(v[t][2 * e], v[t][2 * e + 1]);
+                asm("" : "+v"(h[t][e]));   // keeps the shift below on h (else it re-converts the first value alone)
+                if (X3) l[t][e] = split_lo(v[t][2 * e], v[t][2 * e + 1], h[t][e] << 16, h[t][e] & 0xffff0000u);
+            }
+        char *q = arr + gswz(k, 4 * r + m);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            *(u32x4 *)(q + t * GCHUNK) = u32x4{h[t][0], h[t][1], h[t][2], h[t][3]};
+            if (X3) *(u32x4 *)(q + t * GCHUNK + GARR) = u32x4{l[t][0], l[t][1], l[t][2], l[t][3]};
+        }
+    }
+}
+
+// One 32 x 16 operand at the lane's two base offsets, K step ks.
+__device__ __forceinline__ bf16x8 sum_op(const char *arr, int b0, int b1, int ks) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const int off = 16 * GROW * ks;
+    const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(arr + b0 + off));
+    const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(arr + b1 + off));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 c = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    return __builtin_bit_cast(bf16x8, c);
+}
+
+// A contracting wave's state: operands of both K steps, and its lane's offsets of the chunk being read.
+struct SumCtx {
+    const char *smem;
+    int bx[2][2], by[2][2];
+    bf16x8 ah[2][2], al[2][2], bh[2][2], bl[2][2];
+    f32x16 acc[2][2];
+};
+
+// Operand OP of a K step in the order of first use: ah0, bh0, bh1, ah1, bl0, bl1, al0, al1.
+template <int OP, int KS>
+__device__ __forceinline__ void sum_read(SumCtx &c) {
+    if constexpr (OP == 0) c.ah[KS][0] = sum_op(c.smem, c.bx[0][0], c.bx[0][1], KS);
+    if constexpr (OP == 1) c.bh[KS][0] = sum_op(c.smem, c.by[0][0], c.by[0][1], KS);
+    if constexpr (OP == 2) c.bh[KS][1] = sum_op(c.smem, c.by[1][0], c.by[1][1], KS);
+    if constexpr (OP == 3) c.ah[KS][1] = sum_op(c.smem, c.bx[1][0], c.bx[1][1], KS);
+    if constexpr (OP == 4) c.bl[KS][0] = sum_op(c.smem + GARR, c.by[0][0], c.by[0][1], KS);
+    if constexpr (OP == 5) c.bl[KS][1] = sum_op(c.smem + GARR, c.by[1][0], c.by[1][1], KS);
+    if constexpr (OP == 6) c.al[KS][0] = sum_op(c.smem + GARR, c.bx[0][0], c.bx[0][1], KS);
+    if constexpr (OP == 7) c.al[KS][1] = sum_op(c.smem + GARR, c.bx[1][0], c.bx[1][1], KS);
+}
+constexpr int kSumFirstUse[8] = {0, 0, 1, 2, 4, 5, 8, 10};   // slot of the K step
+constexpr int kSumAhead = 6;                                 // slots between a read and its first use
+constexpr int sum_read_slot(int op, int ks) { return (kSumFirstUse[op] + 12 * ks - kSumAhead + 24) % 24; }
+// The slot after which the lane's offsets move on to the next chunk: every read before it is of this chunk,
+// every read after it of the next.
+constexpr int kSumMove = 16;
+constexpr bool sum_plan_ok() {
+    for (int op = 0; op < 8; ++op)
+        for (int ks = 0; ks < 2; ++ks) {
+            const int t = kSumFirstUse[op] + 12 * ks - kSumAhead;   // negative: in the chunk before
+            if (t < 0 ? t + 24 <= kSumMove : t > kSumMove) return false;
+        }
+    return true;
+}
+static_assert(sum_plan_ok(), "reads of this chunk before the move, of the next after it");
+
+template <int I, int... OP>
+__device__ __forceinline__ void sum_reads_at(SumCtx &c, std::integer_sequence<int, OP...>) {
+    ((sum_read_slot(OP & 7, OP >> 3) == I ? sum_read<OP & 7, (OP >> 3)>(c) : void()), ...);
+}
+
+// The hi operands of K step ks of the chunk at byte `off`.
+__device__ __forceinline__ void sum_read_plain(SumCtx &c, int ks, int off) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        c.ah[ks][t] = sum_op(c.smem + off, c.bx[t][0], c.bx[t][1], ks);
+        c.bh[ks][t] = sum_op(c.smem + off, c.by[t][0], c.by[t][1], ks);
+    }
+}
+
+// Slot I of a three-product chunk: one MFMA (per K step the passes hi * hi, hi * lo, lo * hi over the four
+// accumulator tiles) and the operand reads that are due.  FRESH: the chunk begins its split.  NEXT: the first
+// operands of the next chunk are read in this one's last slots (else it lies behind a barrier).
+template <int I, bool FRESH, bool NEXT>
+__device__ __forceinline__ void sum_slot(SumCtx &c) {
+    constexpr int ks = I / 12, pass = I % 12 / 4, a = I % 4 / 2, b = I % 2;
+    const bf16x8 A = pass == 2 ? c.al[ks][a] : c.ah[ks][a];
+    const bf16x8 B = pass == 1 ? c.bl[ks][b] : c.bh[ks][b];
+    if constexpr (FRESH && I < 4) {
+        f32x16 zero;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero[e] = 0.0f;
+        c.acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, zero, 0, 0, 0);
+    } else {
+        c.acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B, c.acc[a][b], 0, 0, 0);
+    }
+    if constexpr (NEXT || I <= kSumMove) sum_reads_at<I>(c, std::make_integer_sequence<int, 16>{});
+    if constexpr (I == kSumMove) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int rd = 0; rd < 2; ++rd) {
+                c.bx[t][rd] = (c.bx[t][rd] + GCHUNK) & (GRING * GCHUNK - 1);
+                c.by[t][rd] = (c.by[t][rd] + GCHUNK) & (GRING * GCHUNK - 1);
+            }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <bool FRESH, bool NEXT, int... I>
+__device__ __forceinline__ void sum_slots(SumCtx &c, std::integer_sequence<int, I...>) {
+    (sum_slot<I, FRESH, NEXT>(c), ...);
+}
+// The reads that the slots of a chunk before the first would have made.
+template <int... OP>
+__device__ __forceinline__ void sum_first_reads(SumCtx &c, std::integer_sequence<int, OP...>) {
+    ((kSumFirstUse[OP] < kSumAhead ? sum_read<OP, 0>(c) : void()), ...);
+}
+
+template <bool X3, bool ONE>
+__global__ __launch_bounds__(512) void k_fwd_sum_bf16(int64_t n, int Mu, int Mp, const PhaseRec *__restrict__ tx,
+                                                      const PhaseRec *__restrict__ ty, const RunSeed *__restrict__ sx,
+                                                      const RunSeed *__restrict__ sy, double *__restrict__ part,
+                                                      int tiles_p, int64_t chunks, int cps, int64_t chunks_per_group) {
+    __shared__ __attribute__((aligned(16))) char smem[GRING * GCHUNK];   // two pairs of chunks
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t rows = phase_rows(n);
+    int tile;
+    int64_t group;
+    fwd_tile_split(tile, group);
+    const int tu0 = (tile / tiles_p) * GT, tp0 = (tile % tiles_p) * GT;
+    const int64_t c_begin = group * chunks_per_group;
+    const int len = (int)(min(chunks, c_begin + chunks_per_group) - c_begin);
+
+    // Barrier j (from 0) makes pair j visible, which is contracted while pair j + 1 is generated.
+    if (wave >= 4) {
+        // Generator: waves 4 and 5 the X runs, 6 and 7 the Y runs, one run of each chunk a thread.
+        const int axis = (wave >> 1) & 1;
+        const int k = tid & 31, r = (tid >> 5) & 3;
+        const int f0 = (axis ? tp0 : tu0) + 32 * r;
+        const PhaseRec *tab = axis ? ty : tx;
+        const RunSeed *seeds = axis ? sy : sx;
+        char *dst = smem + axis * 2 * GARR;
+        // (chunks past the range: zero records or records of the next group, generated and never used)
+        auto rec = [&](int c) { return load_gen(tab, seeds, rows, f0 / 32, min(c_begin + c, chunks) * FKB + k); };
+        __builtin_amdgcn_s_setprio(1);   // the slower half first (without: 443 us for 401)
+        GenRec R0 = rec(0), R1 = rec(1);
+        for (int c = 0; c < len + 2; c += 2) {
+            const GenRec Q0 = R0, Q1 = R1;
+            R0 = rec(c + 2);
+            R1 = rec(c + 3);
+            if (c < len) sum_gen<X3>(Q0, Q1, f0, dst + (c & 2) * GCHUNK, k, r);
+            lds_barrier();
+        }
+        return;
+    }
+
+    // Contraction: wave w the 64 x 64 sub-tile (u-half w % 2, p-half w / 2).
+    const int wu = 64 * (wave & 1), wp = 64 * (wave >> 1);
+    SumCtx ctx;
+    ctx.smem = smem;
+    {
+        const int q = lane >> 4, i = lane & 15;
+#pragma unroll
+        for (int rd = 0; rd < 2; ++rd) {
+            const int row = 8 * (q >> 1) + (i >> 2) + 4 * rd;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const int cx = wu + 32 * a + 16 * (q & 1) + 4 * (i & 3), cy = wp + 32 * a + 16 * (q & 1) + 4 * (i & 3);
+                ctx.bx[a][rd] = gswz(row, cx >> 3) + (cx & 7) * 2;
+                ctx.by[a][rd] = gswz(row, cy >> 3) + (cy & 7) * 2 + 2 * GARR;
+            }
+        }
+    }
+    double sum[2][2][16];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sum[a][b][e] = 0.0, ctx.acc[a][b][e] = 0.0f;
+
+    lds_barrier();
+    int done = 0;   // chunks of the current split that acc holds
+    auto flush = [&](bool last) __attribute__((always_inline)) {
+        if (ONE || ++done == cps || last) {
+            done = 0;
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        sum[a][b][e] += (double)ctx.acc[a][b][e];
+                        if (!ONE || !X3) ctx.acc[a][b][e] = 0.0f;
+                    }
+        }
+    };
+    auto chunk = [&](int c, auto second) __attribute__((always_inline)) {
+        if constexpr (X3) {
+            sum_slots<ONE, !decltype(second)::value>(ctx, std::make_integer_sequence<int, 24>{});
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                sum_read_plain(ctx, ks, (c & (GRING - 1)) * GCHUNK);
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        ctx.acc[a][b] =
+                            __builtin_amdgcn_mfma_f32_32x32x16_bf16(ctx.ah[ks][a], ctx.bh[ks][b], ctx.acc[a][b], 0, 0, 0);
+            }
+        }
+        flush(c + 1 == len);
+    };
+    for (int c = 0; c < len; c += 2) {
+        if (X3) sum_first_reads(ctx, std::make_integer_sequence<int, 8>{});
+        chunk(c, std::false_type{});
+        if (c + 1 < len) chunk(c + 1, std::true_type{});
+        lds_barrier();
+    }
+
+    double *out = part + (size_t)group * (size_t)Mu * (size_t)Mp;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int u = tu0 + wu + 32 * a + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                const int p = tp0 + wp + 32 * b + (lane & 31);
+                if (u < Mu && p < Mp) out[(size_t)u * Mp + p] = sum[a][b][e];
+            }
+}
+
 // ================================================================================================
 // Backward: G[i][nn] = sum_k A_ik B[k][nn], g_i = sum_nn E_i,nn G[i][nn].
 // Kernels: k_bwd1_bf16 (the basis regenerated, one wave per SIMD, three products or one, further
@@ -1641,6 +1917,20 @@ hipError_t launch_fwd_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp
     else
         hipLaunchKernelGGL(k_fwd1_bf16<false>, grid, dim3(256), 0, s, n, Mu, Mp, tx, ty, sx, sy, part, pl.tiles_p,
                            pl.chunks, pl.chunks_per_split, 0, 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_fwd_sum_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
+                               const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, double *part, hipStream_t s) {
+    const int tiles_p = (Mp + GT - 1) / GT;
+    const dim3 grid((Mu + GT - 1) / GT * tiles_p, pl.groups);
+    const int64_t per = pl.splits_per_group * pl.chunks_per_split;
+    const int cps = (int)pl.chunks_per_split;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(512), 0, s, n, Mu, Mp, tx, ty, sx, sy, part, tiles_p, pl.chunks, cps, per);
+    };
+    if (x3) cps == 1 ? go(k_fwd_sum_bf16<true, true>) : go(k_fwd_sum_bf16<true, false>);
+    else cps == 1 ? go(k_fwd_sum_bf16<false, true>) : go(k_fwd_sum_bf16<false, false>);
     return hipGetLastError();
 }
 
