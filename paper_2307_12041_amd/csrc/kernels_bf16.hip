@@ -1285,7 +1285,7 @@ struct AGen {
     __device__ __forceinline__ bf16x8 lo() const { return __builtin_bit_cast(bf16x8, u32x4{ll[0], ll[1], ll[2], ll[3]}); }
 };
 
-template <int KA>
+template <int KA, int RT>
 struct Bwd1Ctx {
     const char *cur, *nxt;
     char *cpy_dst;                 // released buffer receiving the chunk after next (after the barrier)
@@ -1294,10 +1294,10 @@ struct Bwd1Ctx {
     unsigned cpy_off2;             // its byte offset in the operand (past the last chunk: the last chunk again)
     const char *gtile;             // the N tile's operand, Q chunks of 64 KB
     int gbytes;                    // its size
-    AGen<KA> (&g)[2];
-    bf16x8 (&ah)[2], (&al)[2];     // A operands of the current step
+    AGen<KA> (&g)[RT];
+    bf16x8 (&ah)[RT], (&al)[RT];   // A operands of the current step
     bf16x8 (&bh)[8], (&bl)[8];     // B operands
-    f32x16 (&acc)[2][8];
+    f32x16 (&acc)[RT][8];
     int h, j;
     unsigned lane_off;             // this lane's byte offset within a copy slice
     int wave_off;                  // 1024 times the wave's index (uniform)
@@ -1318,8 +1318,8 @@ __device__ __forceinline__ void bwd1_copy16(const char *gtile, int gbytes, unsig
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)gtile, (short)0, gbytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)lds, 16, voff, soff, IMM, 0);
 }
-template <int SL, int NSL, bool NEXT, int KA>
-__device__ __forceinline__ void bwd1_copy_slice(const Bwd1Ctx<KA> &c) {
+template <int SL, int NSL, bool NEXT, int KA, int RT>
+__device__ __forceinline__ void bwd1_copy_slice(const Bwd1Ctx<KA, RT> &c) {
     static_assert(NSL % 4 == 0 && SL >= 0 && SL < NSL, "copy slices");
     constexpr int grp = (SL >> 2) * 4096;
     const int part = NSL * c.wave_off + grp;
@@ -1362,32 +1362,47 @@ constexpr int bwd1x3_copy_next(int slot) {
 }
 constexpr int bwd1x3_copy_after(int slot) { return slot == 188 ? 0 : slot == 190 ? 1 : -1; }
 
+// A chunk's slots with RT subtiles a wave: slots of a step and of the chunk, the slot that the barrier follows, and the
+// slots of a step in which lo B (of this step) and hi B (of the next one) are read.
+template <bool X3, int RT>
+struct Bwd1Plan {
+    static constexpr int kStep = (X3 ? 24 : 8) * RT, kSlots = 4 * kStep, kSlices = X3 ? 16 : 8;
+    static constexpr int kLo = X3 ? 8 * RT : -8, kHi = X3 ? 16 * RT : RT == 2 ? 8 : 0;
+    static constexpr int kBarrier = 3 * kStep + kHi - 1;
+    static constexpr int copy_after(int slot) {
+        return X3 && RT == 2 ? bwd1x3_copy_after(slot) : bwd1_copy_after<kBarrier, 4>(slot);
+    }
+    static constexpr int copy_next(int slot) {
+        return X3 && RT == 2 ? bwd1x3_copy_next(slot) : bwd1_copy_next<kSlices, !X3 && RT == 1 ? 2 : 4>(slot);
+    }
+};
+
 // Compile-time check of the copy plans against the chunk's reads and barrier, for 1 to 6 chunks.
 // Copies land at the barrier's wait (each wave waits for its own, then all meet), and waves are
 // ordered only by barriers, so: every read of a buffer finds there the whole operand tile of the
-// chunk it expects (NSL slices), none of it still in flight, and a copy writes a buffer only when
-// every read of that buffer lies at or before the last barrier.  Reads: three products, lo B at
-// slots 16-23 and hi B at slots 32-39 of each step (the next chunk's hi B, from the other buffer, in
-// step 3), barrier after slot 175; one product, hi B at slots 8-15 of each step (the next chunk's in
-// step 3), barrier after slot 55.
-template <bool X3>
+// chunk it expects (all slices), none of it still in flight, and a copy writes a buffer only when
+// every read of that buffer lies at or before the last barrier.  Reads: lo B in eight slots of each step from kLo
+// on, hi B of the next step in eight from kHi on (of the next chunk, from the other buffer, in step 3).
+template <bool X3, int RT>
 constexpr bool bwd1_copy_plan_ok() {
-    constexpr int NS = X3 ? 192 : 64, BAR = X3 ? 175 : 55, NSL = X3 ? 16 : 8, STEP = X3 ? 48 : 16;
+    typedef Bwd1Plan<X3, RT> P;
+    int copies = 0;
+    for (int i = 0; i < P::kSlots; ++i) copies += (P::copy_after(i) >= 0) + (P::copy_next(i) >= 0);
+    if (copies != P::kSlices) return false;
     for (int Q = 1; Q <= 6; ++Q) {
         int have[2][16] = {}, src[2][16] = {};
         bool pend[2][16] = {};
         int lastread[2] = {-1, -1}, lastbar = -1;
         for (int b = 0; b < 2; ++b)
             for (int sl = 0; sl < 16; ++sl) have[b][sl] = -1;
-        for (int sl = 0; sl < NSL; ++sl) have[0][sl] = 0;       // prologue: chunk 0,
-        if (Q > 1) have[1][0] = have[1][1] = 1;                 // the first two slices of chunk 1
+        for (int sl = 0; sl < P::kSlices; ++sl) have[0][sl] = 0;   // prologue: chunk 0,
+        if (Q > 1) have[1][0] = have[1][1] = 1;                    // the first two slices of chunk 1
         for (int q = 0; q < Q; ++q) {
             const int cur = q & 1, nxt = cur ^ 1;
             const int after = q + 2 < Q - 1 ? q + 2 : Q - 1, next = q + 1 < Q - 1 ? q + 1 : Q - 1;
-            for (int i = 0; i < NS; ++i) {
-                const int g = q * NS + i, s = i / STEP, t = i % STEP;
-                const int ca = X3 ? bwd1x3_copy_after(i) : bwd1_copy_after<55, 4>(i);
-                const int cn = X3 ? bwd1x3_copy_next(i) : bwd1_copy_next<8, 4>(i);
+            for (int i = 0; i < P::kSlots; ++i) {
+                const int g = q * P::kSlots + i, s = i / P::kStep, t = i % P::kStep;
+                const int ca = P::copy_after(i), cn = P::copy_next(i);
                 if (ca >= 0) {
                     if (lastread[cur] > lastbar) return false;
                     pend[cur][ca] = true;
@@ -1399,15 +1414,15 @@ constexpr bool bwd1_copy_plan_ok() {
                     src[nxt][cn] = next;
                 }
                 int rb = -1, need = 0;   // buffer read in this slot and the chunk it must hold
-                if (X3 && t >= 16 && t < 24) rb = cur, need = q;
-                if (t >= (X3 ? 32 : 8) && t < (X3 ? 40 : 16)) rb = s < 3 ? cur : nxt, need = s < 3 ? q : q + 1;
+                if (P::kLo >= 0 && t >= P::kLo && t < P::kLo + 8) rb = cur, need = q;
+                if (t >= P::kHi && t < P::kHi + 8) rb = s < 3 ? cur : nxt, need = s < 3 ? q : q + 1;
                 if (rb >= 0) {
                     if (need < Q)
-                        for (int sl = 0; sl < NSL; ++sl)
+                        for (int sl = 0; sl < P::kSlices; ++sl)
                             if (pend[rb][sl] || have[rb][sl] != need) return false;
                     lastread[rb] = g;
                 }
-                if (i == BAR) {
+                if (i == P::kBarrier) {
                     for (int b = 0; b < 2; ++b)
                         for (int sl = 0; sl < 16; ++sl)
                             if (pend[b][sl]) have[b][sl] = src[b][sl], pend[b][sl] = false;
@@ -1418,7 +1433,9 @@ constexpr bool bwd1_copy_plan_ok() {
     }
     return true;
 }
-static_assert(bwd1_copy_plan_ok<true>() && bwd1_copy_plan_ok<false>(), "copy plan hazard");
+static_assert(bwd1_copy_plan_ok<true, 2>() && bwd1_copy_plan_ok<false, 2>() && bwd1_copy_plan_ok<true, 1>() &&
+                  bwd1_copy_plan_ok<false, 1>(),
+              "copy plan hazard");
 
 // B operand of column tile b, K step s of a chunk buffer: row 32 b + j, logical segment 4 h + s,
 // physical segment XORed with (j / 2) % 8.
@@ -1436,31 +1453,46 @@ __device__ __forceinline__ bf16x8 bwd1_readb(const char *buf, int hl, int b, int
 // first used at slot 16; the hi operands are assembled at slot 47.  In step 0 the phasor jump
 // takes the second-FMA slots 1-22; in step 2 each subtile is reseeded from its phasors after its
 // last value of the chunk.
-template <int KA, int GS, bool FIRST0, int T>
-__device__ __forceinline__ void bwd1_gen(Bwd1Ctx<KA> &c) {
+// With one subtile (RT = 1) value e takes slots 3 e and 3 e + 1 of 24; its pair m is complete at e = 2 m + 1, whose third slot
+// splits the hi half off, the next value's the lo half.
+template <int KA, int RT, int GS, bool FIRST0, int T>
+__device__ __forceinline__ void bwd1_gen(Bwd1Ctx<KA, RT> &c) {
     constexpr int u = T / 3, ph = T % 3;
-    constexpr int a = u & 1, e = u >> 1;
-    if constexpr (ph == 0) c.g[a].template value1<e, FIRST0>();
-    if constexpr (ph == 1) c.g[a].value2();
-    if constexpr (ph == 2) {
-        // hi halves at u = 4 m + 2 + a, lo halves (m < 3) at u = 4 m + 4 + a, lo of pair 3 at u = a
-        constexpr int r4 = u & 3;
-        if constexpr (r4 >= 2) c.g[r4 - 2].template half_hi<(u >> 2)>();
-        else if constexpr (u >= 4) c.g[r4].template half_lo<(u >> 2) - 1>();
-        else c.g[r4].template half_lo<3>();
+    if constexpr (RT == 2) {
+        constexpr int a = u & 1, e = u >> 1;
+        if constexpr (ph == 0) c.g[a].template value1<e, FIRST0>();
+        if constexpr (ph == 1) c.g[a].value2();
+        if constexpr (ph == 2) {
+            // hi halves at u = 4 m + 2 + a, lo halves (m < 3) at u = 4 m + 4 + a, lo of pair 3 at u = a
+            constexpr int r4 = u & 3;
+            if constexpr (r4 >= 2) c.g[r4 - 2].template half_hi<(u >> 2)>();
+            else if constexpr (u >= 4) c.g[r4].template half_lo<(u >> 2) - 1>();
+            else c.g[r4].template half_lo<3>();
+        }
+        if constexpr (GS == 0 && ph == 1 && u < 8) c.g[u >> 2].template jump<u & 3>();
+        if constexpr (GS == 2 && T == 45) c.g[0].reseed();
+        if constexpr (GS == 2 && T == 47) c.g[1].reseed();
+    } else {
+        if constexpr (ph == 0) c.g[0].template value1<u, FIRST0>();
+        if constexpr (ph == 1) c.g[0].value2();
+        if constexpr (ph == 2) {
+            if constexpr (u & 1) c.g[0].template half_hi<(u >> 1)>();
+            else if constexpr (u >= 2) c.g[0].template half_lo<(u >> 1) - 1>();
+            else c.g[0].template half_lo<3>();
+        }
+        if constexpr (GS == 0 && ph == 1 && u < 4) c.g[0].template jump<u>();
+        if constexpr (GS == 2 && T == 23) c.g[0].reseed();
     }
-    if constexpr (GS == 0 && ph == 1 && u < 8) c.g[u >> 2].template jump<u & 3>();
-    if constexpr (GS == 2 && T == 45) c.g[0].reseed();
-    if constexpr (GS == 2 && T == 47) c.g[1].reseed();
 }
 
-// Slot I (0..191) of a chunk: one MFMA, the B reads, copies and generator work assigned to it, then
+// Slot I (0..191; 0..95 with one subtile) of a chunk: one MFMA, the B reads, copies and generator work assigned to it, then
 // a scheduling fence.  MFMA order within a step: pass (hi*hi, lo*hi, hi*lo), column tile b,
 // subtile a.
-template <int KA, int I>
-__device__ __forceinline__ void bwd1_slot(Bwd1Ctx<KA> &c) {
-    constexpr int s = I / 48, t = I % 48;
-    constexpr int pass = t / 16, b = (t % 16) / 2, a = t % 2;
+template <int KA, int RT, int I>
+__device__ __forceinline__ void bwd1_slot(Bwd1Ctx<KA, RT> &c) {
+    typedef Bwd1Plan<true, RT> P;
+    constexpr int s = I / P::kStep, t = I % P::kStep;
+    constexpr int pass = t / (8 * RT), b = t % (8 * RT) / RT, a = t % RT;
     {
         const bf16x8 A = pass == 1 ? c.al[a] : c.ah[a];
         const bf16x8 B = pass == 2 ? c.bl[b] : c.bh[b];
@@ -1470,35 +1502,35 @@ __device__ __forceinline__ void bwd1_slot(Bwd1Ctx<KA> &c) {
     // issued ahead of it, and the wait for the MFMA's own operand then covers that fresh read too.
     __builtin_amdgcn_sched_barrier(0);
     // lo B of this step in the first half of the lo*hi pass, hi B of the next step in the first half
-    // of the hi*lo pass: each read lands at least 8 slots before its first use, so that even a full
-    // LDS wait (the compiler's while direct copies are in flight) finds them complete.
-    if constexpr (t >= 16 && t < 24) c.bl[t - 16] = bwd1_readb(c.cur, 1, t - 16, s, c.h, c.j);
-    if constexpr (s == 3 && t == 31) {
+    // of the hi*lo pass (with one subtile in the whole pass): each read lands at least 8 slots before its first use, so
+    // that even a full LDS wait (the compiler's while direct copies are in flight) finds them complete.
+    if constexpr (t >= P::kLo && t < P::kLo + 8) c.bl[t - P::kLo] = bwd1_readb(c.cur, 1, t - P::kLo, s, c.h, c.j);
+    if constexpr (I == P::kBarrier) {
         // all reads of this chunk's buffer are done and the next chunk's copies have landed
         wait_copies();
         lds_barrier();
     }
-    if constexpr (t >= 32 && t < 40) {
-        constexpr int bb = t - 32;
+    if constexpr (t >= P::kHi && t < P::kHi + 8) {
+        constexpr int bb = t - P::kHi;
         if constexpr (s < 3) c.bh[bb] = bwd1_readb(c.cur, 0, bb, s + 1, c.h, c.j);
         else c.bh[bb] = bwd1_readb(c.nxt, 0, bb, 0, c.h, c.j);
     }
     {
         // copies (unconditional, so that the chunk stays one basic block: past the end the last
         // chunk is copied again into a buffer that is not read any more)
-        constexpr int ca = bwd1x3_copy_after(I), cn = bwd1x3_copy_next(I);
-        if constexpr (I == 188) counted_lds_wait();
+        constexpr int ca = P::copy_after(I), cn = P::copy_next(I);
+        if constexpr (RT == 2 && I == 188) counted_lds_wait();
         if constexpr (ca >= 0) bwd1_copy_slice<ca, 16, false>(c);
         if constexpr (cn >= 0) bwd1_copy_slice<cn, 16, true>(c);
     }
-    bwd1_gen<KA, s, false, t>(c);
-    if constexpr (t == 6) {
+    bwd1_gen<KA, RT, s, false, t>(c);
+    if constexpr (t == 3 * RT) {
 #pragma unroll
-        for (int aa = 0; aa < 2; ++aa) c.al[aa] = c.g[aa].lo();
+        for (int aa = 0; aa < RT; ++aa) c.al[aa] = c.g[aa].lo();
     }
-    if constexpr (t == 47) {
+    if constexpr (t == P::kStep - 1) {
 #pragma unroll
-        for (int aa = 0; aa < 2; ++aa) c.ah[aa] = c.g[aa].hi();
+        for (int aa = 0; aa < RT; ++aa) c.ah[aa] = c.g[aa].hi();
     }
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -1510,58 +1542,67 @@ __device__ __forceinline__ void bwd1_slot(Bwd1Ctx<KA> &c) {
 // value of each subtile in step 2.  Next step's hi B is read at slots 8-15, at least 8 slots ahead
 // of its first use and after the current step's last use of the same register; the barrier moves
 // to slot 7 of step 3; the copies (hi halves only) follow bwd1_copy_after and bwd1_copy_next.
-template <int KA, int I>
-__device__ __forceinline__ void bwd1_slot_plain(Bwd1Ctx<KA> &c) {
-    constexpr int s = I / 16, t = I % 16;
-    constexpr int b = t / 2, a = t % 2;
+// With one subtile a step has 8 slots: slot t reads next step's hi B of the column tile that it has just contracted, and the
+// barrier precedes step 3.
+template <int KA, int RT, int I>
+__device__ __forceinline__ void bwd1_slot_plain(Bwd1Ctx<KA, RT> &c) {
+    typedef Bwd1Plan<false, RT> P;
+    constexpr int s = I / P::kStep, t = I % P::kStep;
+    constexpr int b = t / RT, a = t % RT;
     c.acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.ah[a], c.bh[b], c.acc[a][b], 0, 0, 0);
-    if constexpr (s == 3 && t == 7) {
+    if constexpr (RT == 2 && I == P::kBarrier) {
         wait_copies();
         lds_barrier();
     }
-    if constexpr (t >= 8) {
-        constexpr int bb = t - 8;
+    if constexpr (t >= P::kHi) {
+        constexpr int bb = t - P::kHi;
         if constexpr (s < 3) c.bh[bb] = bwd1_readb(c.cur, 0, bb, s + 1, c.h, c.j);
         else c.bh[bb] = bwd1_readb(c.nxt, 0, bb, 0, c.h, c.j);
     }
+    if constexpr (RT == 1 && I == P::kBarrier) {   // the slot's own read is of the buffer that the barrier releases
+        wait_copies();
+        lds_barrier();
+    }
     {
-        constexpr int ca = bwd1_copy_after<55, 4>(I), cn = bwd1_copy_next<8, 4>(I);
-        static_assert(55 + 1 + 4 < 64 && 4 * 5 < 55 - 24, "copy plan");
+        constexpr int ca = P::copy_after(I), cn = P::copy_next(I);
         if constexpr (ca >= 0) bwd1_copy_slice<ca, 8, false>(c);
         if constexpr (cn >= 0) bwd1_copy_slice<cn, 8, true>(c);
     }
     {
-        constexpr int u = t, ga = u & 1, e = u >> 1;
+        constexpr int u = t, ga = u % RT, e = u / RT;
         c.g[ga].template value1<e, false>();
         c.g[ga].value2();
-        if constexpr ((u & 3) >= 2) c.g[ga].template pack_hi<(u >> 2)>();
-        if constexpr (s == 0 && u < 8) {
+        if constexpr (e & 1) c.g[ga].template pack_hi<(e >> 1)>();
+        if constexpr (s == 0 && u < 4 * RT) {
             c.g[u >> 2].template jump<(u & 3)>();
         }
-        if constexpr (s == 2 && u == 14) c.g[0].reseed();
-        if constexpr (s == 2 && u == 15) c.g[1].reseed();
+        if constexpr (s == 2 && u == 7 * RT) c.g[0].reseed();
+        if constexpr (RT == 2 && s == 2 && u == 15) c.g[1].reseed();
     }
-    if constexpr (t == 15) {
+    if constexpr (t == P::kStep - 1) {
 #pragma unroll
-        for (int aa = 0; aa < 2; ++aa) c.ah[aa] = c.g[aa].hi();
+        for (int aa = 0; aa < RT; ++aa) c.ah[aa] = c.g[aa].hi();
     }
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool X3, int KA, int... I>
-__device__ __forceinline__ void bwd1_slots(Bwd1Ctx<KA> &c, std::integer_sequence<int, I...>) {
-    if constexpr (X3) (bwd1_slot<KA, I>(c), ...);
-    else (bwd1_slot_plain<KA, I>(c), ...);
+template <bool X3, int KA, int RT, int... I>
+__device__ __forceinline__ void bwd1_slots(Bwd1Ctx<KA, RT> &c, std::integer_sequence<int, I...>) {
+    if constexpr (X3) (bwd1_slot<KA, RT, I>(c), ...);
+    else (bwd1_slot_plain<KA, RT, I>(c), ...);
 }
 
-template <int KA, bool FIRST0, int... T>
-__device__ __forceinline__ void bwd1_gen_all(Bwd1Ctx<KA> &c, std::integer_sequence<int, T...>) {
-    (bwd1_gen<KA, 1, FIRST0, T>(c), ...);
+template <int KA, bool FIRST0, int RT, int... T>
+__device__ __forceinline__ void bwd1_gen_all(Bwd1Ctx<KA, RT> &c, std::integer_sequence<int, T...>) {
+    (bwd1_gen<KA, RT, 1, FIRST0, T>(c), ...);
 }
 
 
 // X3: three products per pair (hi*hi, lo*hi, hi*lo); otherwise one (hi*hi).
-template <bool X3, int KA, int E1, int E2>
+// RT: 32-block subtiles of a wave.  Two keep the matrix cores at 92 % within a chunk (6700 cycles for 192 MFMAs beside 650
+// vector instructions).  One halves a workgroup's work where two would leave CUs idle (see launch_rowform_bf16): its chunk
+// takes 0.6 of the other's, its epilogue half (two column tiles at a time).  Same products and sums in FP32 either way.
+template <bool X3, int KA, int E1, int E2, int RT>
 __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf16> P) {
     __shared__ __attribute__((aligned(16))) char smem[2 * BBUF];
     const bool second = (int)blockIdx.y >= P.tiles0;
@@ -1570,21 +1611,21 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, j = lane & 31;
     const int btile = blockIdx.x, ntile = (int)blockIdx.y - (second ? P.tiles0 : 0) + ax.nt0;
-    const int64_t i0 = (int64_t)btile * 256 + 64 * wave;
+    const int64_t i0 = (int64_t)btile * (128 * RT) + 32 * RT * wave;
     const int n0 = ntile * BTN;
     const int Q = ax.Kh / 32;
     const size_t tile_bytes = (size_t)BBUF;
     const char *gb = (const char *)ax.B + (size_t)ntile * Q * tile_bytes;
 
-    AGen<KA> g[2];
+    AGen<KA> g[RT];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < RT; ++a) {
         const int64_t ib = i0 + 32 * a + j;
         g[a].init(ax.ta, ib, ib < n, h * ax.Kh);
     }
-    f32x16 acc[2][8];
+    f32x16 acc[RT][8];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < RT; ++a)
 #pragma unroll
         for (int b = 0; b < 8; ++b)
 #pragma unroll
@@ -1597,18 +1638,18 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
     for (int sl = 0; sl < BBUF / 4096; ++sl)
         __builtin_amdgcn_global_load_lds((const void *)(gb + sl * 4096 + tid * 16),
                                          (lds_void *)(smem + sl * 4096 + wave * 1024), 16, 0, 0);
-    bf16x8 ah[2], al[2], bh[8], bl[8];
-    Bwd1Ctx<KA> c{smem, smem + BBUF, smem + BBUF, Q > 1 ? (unsigned)BBUF : 0u, smem + BBUF, 0u, gb, Q * BBUF,
+    bf16x8 ah[RT], al[RT], bh[8], bl[8];
+    Bwd1Ctx<KA, RT> c{smem, smem + BBUF, smem + BBUF, Q > 1 ? (unsigned)BBUF : 0u, smem + BBUF, 0u, gb, Q * BBUF,
                   g, ah, al, bh, bl, acc, h, j, (unsigned)lane * 16u, wave * 1024};
     if (Q > 1) {
         bwd1_copy_slice<0, X3 ? 16 : 8, false>(c);
         bwd1_copy_slice<1, X3 ? 16 : 8, false>(c);
     }
-    if (h == 0) bwd1_gen_all<KA, true>(c, std::make_integer_sequence<int, 48>{});
-    else bwd1_gen_all<KA, false>(c, std::make_integer_sequence<int, 48>{});
+    if (h == 0) bwd1_gen_all<KA, true>(c, std::make_integer_sequence<int, 24 * RT>{});
+    else bwd1_gen_all<KA, false>(c, std::make_integer_sequence<int, 24 * RT>{});
     // the lo halves of pair 3 (in the loop: slots 2 and 5 of the next step)
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < RT; ++a) {
         g[a].template half_lo<3>();
         ah[a] = g[a].hi();
         al[a] = g[a].lo();
@@ -1626,7 +1667,7 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
         c.cpy_off = (unsigned)min(q + 2, Q - 1) * (unsigned)BBUF;
         c.cpy_dst2 = smem + ((q & 1) ^ 1) * BBUF;
         c.cpy_off2 = (unsigned)min(q + 1, Q - 1) * (unsigned)BBUF;
-        bwd1_slots<X3>(c, std::make_integer_sequence<int, X3 ? 192 : 64>{});
+        bwd1_slots<X3>(c, std::make_integer_sequence<int, Bwd1Plan<X3, RT>::kSlots>{});
     }
     wait_copies();   // the copies issued in the last chunks must land before the buffers are reused
     __syncthreads();
@@ -1637,20 +1678,23 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
     // banks), after which lane l holds row l and walks its 32 columns with the epilogue recurrences.
     constexpr int EPS = 36;
     float *tb = (float *)smem + wave * (64 * EPS);
-    const int64_t ibr = i0 + lane;
+    // With one subtile two column tiles are walked at a time, the even one by the lower half wave, the odd one by the upper.
+    const int64_t ibr = i0 + (RT == 2 ? lane : j);
     const bool rvalid = ibr < n;
     EGen<E1, E2> eg;
     if (rvalid) eg.init(ax.te[ibr], n0, ax.pil);
     else eg.init(PhaseRec{}, n0, ax.pil);
+    if (RT == 1 && h) eg.rotate();
     // Each 32-column run is summed in FP32, the runs of the tile in FP64.
     double sum = 0.0, sum2 = 0.0;
     float g00 = 0.0f;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < 8; b += 3 - RT) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) tb[(32 * a + 8 * (r >> 2) + 4 * h + (r & 3)) * EPS + j] = acc[a][b][r];
+            for (int r = 0; r < 16; ++r)
+                tb[(32 * a + 8 * (r >> 2) + 4 * h + (r & 3)) * EPS + j] = RT == 2 ? acc[a * (RT - 1)][b][r] : acc[0][b + a * (2 - RT)][r];
         float gv[32];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -1659,7 +1703,7 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
         }
         if (b == 0) g00 = gv[0];
         eg.seed();
-        float nnp = (float)(n0 + 32 * b) * eg.pil;   // nn pi / L for the w sin kind
+        float nnp = (float)(n0 + 32 * (RT == 2 ? b : b + h)) * eg.pil;   // nn pi / L for the w sin kind
         float run = 0.0f, run2 = 0.0f;
 #pragma unroll
         for (int k = 0; k < 32; ++k) {
@@ -1678,6 +1722,11 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
         sum += (double)run;
         if constexpr (EGen<E1, E2>::DUAL) sum2 += (double)run2;
         eg.rotate();
+        if constexpr (RT == 1) eg.rotate();
+    }
+    if constexpr (RT == 1) {
+        sum += __shfl_xor(sum, 32);
+        if constexpr (EGen<E1, E2>::DUAL) sum2 += __shfl_xor(sum2, 32);
     }
     // kind factors: -2 sin sin (cosine differences), 2 cos sin (sine differences, nn = 0: the size)
     if constexpr (E1 == RUN_COSDIFF) sum *= -2.0;
@@ -1685,7 +1734,7 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
         sum *= 2.0;
         if (n0 == 0) sum += (double)eg.size * (double)g00;   // 2 cos sin vanishes at nn = 0
     }
-    if (rvalid) {
+    if (rvalid && (RT == 2 || h == 0)) {
         if (ax.out.r) {
             const double d = ax.out.dE ? *ax.out.dE : 1.0;
             ax.out.r[ibr] = d * sum;
@@ -1964,9 +2013,16 @@ hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax0, const
         tiles[k] = nt_end - ax.nt0;
     }
     P.tiles0 = tiles[0];
-    dim3 grid((unsigned)((n + 255) / 256), (unsigned)(tiles[0] + tiles[1]));
-    if (x3) hipLaunchKernelGGL((k_bwd1_bf16<true, KA, E1, E2>), grid, dim3(256), 0, s, n, P);
-    else hipLaunchKernelGGL((k_bwd1_bf16<false, KA, E1, E2>), grid, dim3(256), 0, s, n, P);
+    // 256 workgroups run at a time.  Workgroups of 128 blocks take about 0.62 of the time of those of 256 and are twice as
+    // many: they are chosen where their rounds are the shorter ones, as a rule in launches of at most 128 of the larger (n = 5,000,
+    // 257 x 513, both contractions: 100 workgroups 37.4 us, 200 of the half size 24.2) or of just over a round of them (n = 18,000,
+    // 512 x 512: 87 and 78 us; 1,000 blocks, 1024 x 1024: 71 and 49; with one product 45 and 36).
+    const int64_t nt = tiles[0] + tiles[1], rounds2 = ((n + 255) / 256 * nt + 255) / 256, rounds1 = ((n + 127) / 128 * nt + 255) / 256;
+    const bool one = 0.62 * (double)rounds1 < (double)rounds2;
+    const dim3 grid((unsigned)(one ? (n + 127) / 128 : (n + 255) / 256), (unsigned)nt);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, n, P); };
+    if (x3) one ? go(k_bwd1_bf16<true, KA, E1, E2, 1>) : go(k_bwd1_bf16<true, KA, E1, E2, 2>);
+    else one ? go(k_bwd1_bf16<false, KA, E1, E2, 1>) : go(k_bwd1_bf16<false, KA, E1, E2, 2>);
     return hipGetLastError();
 }
 }  // namespace
