@@ -72,7 +72,9 @@ struct Cheb {
 // Epilogue generator of one row (block) along the N axis: the recurrences of the epilogue kinds
 // (sines or cosines of nn alpha, sine of nn beta), reseeded every 32 columns from phasors that
 // advance by the 32-frequency rotations of the phase record.
-template <int E1, int E2>
+// FIRST: which product of the rotated sine is the fused one, the first (bf16) or the second (FP8), as each contraction
+// has always rounded it.
+template <int E1, int E2, bool FIRST = true>
 struct EGen {
     static constexpr bool DUAL = E2 >= 0;
     // chain 0 (alpha): cosine for SINDIFF and COS, sine for COSDIFF and WSIN; chain 1: sine of
@@ -97,22 +99,23 @@ struct EGen {
         size = R.size;
         pil = pil_;
     }
-    // chain values at the current start column nn and nn - 1
+    // chain values at the current start column nn and nn - 1 (here and in rotate() one product rounded, one fused, so
+    // that the values do not depend on the code around)
     __device__ __forceinline__ void seed() {
-        if constexpr (C0_COS) { c0.f = pac; c0.fm = pac * ca1 + pas * sa1; }
-        else { c0.f = pas; c0.fm = pas * ca1 - pac * sa1; }
+        if constexpr (C0_COS) { c0.f = pac; c0.fm = fmaf(pas, sa1, pac * ca1); }
+        else { c0.f = pas; c0.fm = fmaf(pas, ca1, -(pac * sa1)); }
         if constexpr (HAS_C1) {
-            if constexpr (C1_BETA) { c1.f = pbs; c1.fm = pbs * cb1 - pbc * sb1; }
-            else { c1.f = pas; c1.fm = pas * ca1 - pac * sa1; }
+            if constexpr (C1_BETA) { c1.f = pbs; c1.fm = fmaf(pbs, cb1, -(pbc * sb1)); }
+            else { c1.f = pas; c1.fm = fmaf(pas, ca1, -(pac * sa1)); }
         }
     }
     __device__ __forceinline__ void rotate() {
-        const float t = pac * ja_c - pas * ja_s;
-        pas = pas * ja_c + pac * ja_s;
+        const float t = fmaf(pac, ja_c, -(pas * ja_s));
+        pas = FIRST ? fmaf(pas, ja_c, pac * ja_s) : fmaf(pac, ja_s, pas * ja_c);
         pac = t;
         if constexpr (C1_BETA && HAS_C1) {
-            const float tb = pbc * jb_c - pbs * jb_s;
-            pbs = pbs * jb_c + pbc * jb_s;
+            const float tb = fmaf(pbc, jb_c, -(pbs * jb_s));
+            pbs = FIRST ? fmaf(pbs, jb_c, pbc * jb_s) : fmaf(pbc, jb_s, pbs * jb_c);
             pbc = tb;
         }
     }

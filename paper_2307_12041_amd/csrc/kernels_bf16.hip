@@ -1206,7 +1206,8 @@ __global__ __launch_bounds__(512) void k_bwd_bf16_st(int64_t n, BwdAxisBf16 ax) 
 // after 64 jumps ~1e-6), with the values and split halves of the step being generated.  The generator's
 // work is cut into pieces of at most three VALU instructions (a value; the FMAs that advance both
 // recurrences; one half of a hi/lo split; half of a phasor jump), so that the pieces can be dealt
-// over the MFMA slots evenly.
+// over the MFMA slots evenly.  The sums of two products are written as one product rounded and one fused, so that a
+// block's values do not depend on the code around.
 template <int KA>
 struct AGen {
     Cheb ca, sb;
@@ -1232,18 +1233,18 @@ struct AGen {
     }
     __device__ __forceinline__ void reseed() {
         ca.f = pac;
-        ca.fm = pac * sac + pas * sas;                // cos((k - 1) alpha)
+        ca.fm = fmaf(pac, sac, pas * sas);            // cos((k - 1) alpha)
         sb.f = 2.0f * pbs;                            // 2 sin(k beta)
-        sb.fm = 2.0f * (pbs * sbc - pbc * sbs);       // 2 sin((k - 1) beta)
+        sb.fm = 2.0f * fmaf(pbs, sbc, -(pbc * sbs));  // 2 sin((k - 1) beta)
     }
     // The phasors advance by 32 frequencies in four pieces: the new cosine of alpha, then its sine
     // (from the old cosine), then the same for beta.
     template <int P>
     __device__ __forceinline__ void jump() {
-        if constexpr (P == 0) tj0 = pac * jac - pas * jas;
-        else if constexpr (P == 1) { pas = pas * jac + pac * jas; pac = tj0; }
-        else if constexpr (P == 2) tj1 = pbc * jbc - pbs * jbs;
-        else { pbs = pbs * jbc + pbc * jbs; pbc = tj1; }
+        if constexpr (P == 0) tj0 = fmaf(pac, jac, -(pas * jas));
+        else if constexpr (P == 1) { pas = fmaf(pas, jac, pac * jas); pac = tj0; }
+        else if constexpr (P == 2) tj1 = fmaf(pbc, jbc, -(pbs * jbs));
+        else { pbs = fmaf(pbs, jbc, pbc * jbs); pbc = tj1; }
     }
     // Value E of the step (frequency k + E) and the first FMA of each recurrence; at k = 0 the
     // sine-difference kind takes the block size (FIRST0: this step starts at frequency 0).
@@ -1598,20 +1599,15 @@ __device__ __forceinline__ void bwd1_gen_all(Bwd1Ctx<KA, RT> &c, std::integer_se
 }
 
 
-// X3: three products per pair (hi*hi, lo*hi, hi*lo); otherwise one (hi*hi).
-// RT: 32-block subtiles of a wave.  Two keep the matrix cores at 92 % within a chunk (6700 cycles for 192 MFMAs beside 650
+// The blocks from block0 on of a workgroup and one N tile.  RT: 32-block subtiles of a wave.  Two keep the matrix cores at 92 % within a chunk (6700 cycles for 192 MFMAs beside 650
 // vector instructions).  One halves a workgroup's work where two would leave CUs idle (see launch_rowform_bf16): its chunk
 // takes 0.6 of the other's, its epilogue half (two column tiles at a time).  Same products and sums in FP32 either way.
 template <bool X3, int KA, int E1, int E2, int RT>
-__global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf16> P) {
-    __shared__ __attribute__((aligned(16))) char smem[2 * BBUF];
-    const bool second = (int)blockIdx.y >= P.tiles0;
-    const BwdAxisBf16 ax = P.pick(second);
+__device__ __forceinline__ void bwd1_rows(char *smem, int64_t n, const BwdAxisBf16 &ax, int64_t block0, int ntile) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, j = lane & 31;
-    const int btile = blockIdx.x, ntile = (int)blockIdx.y - (second ? P.tiles0 : 0) + ax.nt0;
-    const int64_t i0 = (int64_t)btile * (128 * RT) + 32 * RT * wave;
+    const int64_t i0 = block0 + 32 * RT * wave;
     const int n0 = ntile * BTN;
     const int Q = ax.Kh / 32;
     const size_t tile_bytes = (size_t)BBUF;
@@ -1744,6 +1740,30 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
             if constexpr (EGen<E1, E2>::DUAL) ax.gpart2[(size_t)ntile * (size_t)n + (size_t)ibr] = sum2;
         }
     }
+}
+
+// X3: three products per pair (hi*hi, lo*hi, hi*lo); otherwise one (hi*hi).  A grid of (nb2 + nb1, N tiles), the first nb2
+// N tiles of its workgroups taking 256 blocks each, the rest 128 of the blocks after those; workgroups that follow
+// each other share an N tile.
+template <bool X3, int KA, int E1, int E2>
+__global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf16> P, unsigned nb2, unsigned nb1) {
+    __shared__ __attribute__((aligned(16))) char smem[2 * BBUF];
+    bool two = nb1 == 0;
+    unsigned t = blockIdx.y, b = blockIdx.x;
+    if (nb1 != 0 && nb2 != 0) {
+        unsigned w = blockIdx.y * gridDim.x + blockIdx.x;
+        const unsigned first = nb2 * gridDim.y;
+        two = w < first;
+        if (!two) w -= first;
+        const unsigned nb = two ? nb2 : nb1;
+        t = w / nb;
+        b = w % nb;
+    }
+    const bool second = (int)t >= P.tiles0;
+    const BwdAxisBf16 ax = P.pick(second);
+    const int ntile = (int)t - (second ? P.tiles0 : 0) + ax.nt0;
+    if (two) bwd1_rows<X3, KA, E1, E2, 2>(smem, n, ax, (int64_t)b * 256, ntile);
+    else bwd1_rows<X3, KA, E1, E2, 1>(smem, n, ax, (int64_t)nb2 * 256 + (int64_t)b * 128, ntile);
 }
 
 // Row-form operand preparation for the bf16 path: BT[nn][k] = a_up times the factor of the form
@@ -2013,16 +2033,28 @@ hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax0, const
         tiles[k] = nt_end - ax.nt0;
     }
     P.tiles0 = tiles[0];
-    // 256 workgroups run at a time.  Workgroups of 128 blocks take about 0.62 of the time of those of 256 and are twice as
-    // many: they are chosen where their rounds are the shorter ones, as a rule in launches of at most 128 of the larger (n = 5,000,
-    // 257 x 513, both contractions: 100 workgroups 37.4 us, 200 of the half size 24.2) or of just over a round of them (n = 18,000,
-    // 512 x 512: 87 and 78 us; 1,000 blocks, 1024 x 1024: 71 and 49; with one product 45 and 36).
-    const int64_t nt = tiles[0] + tiles[1], rounds2 = ((n + 255) / 256 * nt + 255) / 256, rounds1 = ((n + 127) / 128 * nt + 255) / 256;
-    const bool one = 0.62 * (double)rounds1 < (double)rounds2;
-    const dim3 grid((unsigned)(one ? (n + 127) / 128 : (n + 255) / 256), (unsigned)nt);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, n, P); };
-    if (x3) one ? go(k_bwd1_bf16<true, KA, E1, E2, 1>) : go(k_bwd1_bf16<true, KA, E1, E2, 2>);
-    else one ? go(k_bwd1_bf16<false, KA, E1, E2, 1>) : go(k_bwd1_bf16<false, KA, E1, E2, 2>);
+    // 256 workgroups run at a time.  A workgroup of 128 blocks takes about 0.62 of the time of one of 256.  Whole rounds of the
+    // larger are followed by the smaller ones where that ends earlier than another round of the larger, and the smaller alone
+    // are taken where those do (whole gradient calls in bf16x3: n = 5,000, 257 x 513, 100 of the larger 39 us, 200 of the smaller
+    // 26; 36,000, 512 x 512, 564 in three rounds 130, 512 and 104 114; 200,050, 512 x 512, 3128 in 13 rounds 534, 3072 and 112
+    // 521; 120,000, 257 x 257, 1876 in eight rounds 221, 1792 and 168 208).
+    const int64_t nt = tiles[0] + tiles[1], all = (n + 255) / 256, whole = all * nt / 256;
+    auto small = [&](int64_t nb2) { return n > nb2 * 256 ? (n - nb2 * 256 + 127) / 128 : 0; };
+    int64_t nb2 = all;
+    if (all * nt < (int64_t)1 << 28) {   // the mixed grid counts its workgroups in 32 bits
+        double best = (double)((all * nt + 255) / 256);
+        for (const int64_t b : {whole * 256 / nt, (int64_t)0}) {
+            const double t = (double)((b * nt + 255) / 256) + 0.62 * (double)((small(b) * nt + 255) / 256);
+            if (t < best) {
+                best = t;
+                nb2 = b;
+            }
+        }
+    }
+    const unsigned nb1 = (unsigned)small(nb2);
+    const dim3 grid((unsigned)nb2 + nb1, (unsigned)nt);
+    if (x3) hipLaunchKernelGGL((k_bwd1_bf16<true, KA, E1, E2>), grid, dim3(256), 0, s, n, P, (unsigned)nb2, nb1);
+    else hipLaunchKernelGGL((k_bwd1_bf16<false, KA, E1, E2>), grid, dim3(256), 0, s, n, P, (unsigned)nb2, nb1);
     return hipGetLastError();
 }
 }  // namespace

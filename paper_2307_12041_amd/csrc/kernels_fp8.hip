@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256) void k_bwd_fp8(int64_t n, BwdAxisFp8 ax) {
     float *tb = (float *)smem + wave * (64 * EPS);
     const int64_t ibr = i0 + lane;
     const bool rvalid = ibr < n;
-    EGen<E1, E2> eg;
+    EGen<E1, E2, false> eg;
     const PhaseRec RE = rvalid ? ax.te[ibr] : PhaseRec{};
     eg.init(RE, n0, ax.pil);
     const float size_k = (rvalid && KA == RUN_SINDIFF) ? ax.ta[ibr].size : 0.0f;   // A_i0 of the K axis
@@ -381,13 +381,13 @@ __global__ __launch_bounds__(256) void k_bwd_fp8(int64_t n, BwdAxisFp8 ax) {
             } else {
                 run = fmaf(nnp * eg.c0.f, gv[k], run);
             }
-            if constexpr (EGen<E1, E2>::DUAL) run2 = fmaf(nnp * eg.c1.f, gv[k], run2);
-            if constexpr (E1 == RUN_WSIN || EGen<E1, E2>::DUAL) nnp += eg.pil;
+            if constexpr (EGen<E1, E2, false>::DUAL) run2 = fmaf(nnp * eg.c1.f, gv[k], run2);
+            if constexpr (E1 == RUN_WSIN || EGen<E1, E2, false>::DUAL) nnp += eg.pil;
             eg.c0.next();
-            if constexpr (EGen<E1, E2>::HAS_C1) eg.c1.next();
+            if constexpr (EGen<E1, E2, false>::HAS_C1) eg.c1.next();
         }
         sum += (double)run;
-        if constexpr (EGen<E1, E2>::DUAL) sum2 += (double)run2;
+        if constexpr (EGen<E1, E2, false>::DUAL) sum2 += (double)run2;
         eg.rotate();
     }
     if constexpr (E1 == RUN_COSDIFF) sum *= -2.0;
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void k_bwd_fp8(int64_t n, BwdAxisFp8 ax) {
     }
     if (rvalid) {
         ax.gpart[(size_t)ntile * (size_t)n + (size_t)ibr] = sum;
-        if constexpr (EGen<E1, E2>::DUAL) ax.gpart2[(size_t)ntile * (size_t)n + (size_t)ibr] = sum2;
+        if constexpr (EGen<E1, E2, false>::DUAL) ax.gpart2[(size_t)ntile * (size_t)n + (size_t)ibr] = sum2;
     }
 }
 

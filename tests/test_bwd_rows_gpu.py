@@ -1,5 +1,6 @@
-"""The bf16 row forms with one and with two 32-block subtiles per wave, on both sides of the line between them: few blocks take
-one, n = 16,385 and more at two N tiles take two.  A block's results do not depend on the other blocks, so the first and the last
+"""The bf16 row forms with one and with two 32-block subtiles per wave, on both sides of the lines between them: few blocks take
+one, n = 16,385 and more at two N tiles take two, n = 33,100 there and n = 13,200 at five N tiles take whole rounds of two and
+the rest of the blocks with one.  A block's results do not depend on the other blocks, so the first and the last
 blocks of a large launch are compared with a launch of them alone (the other kernel), and both with the FP64 oracle.
 
 Bars: the precision's own against the oracle (1e-3, 3e-2); 1e-12 between the kernels (the FP32 run sums are the same bits, the
@@ -25,7 +26,7 @@ def rel(a, b):
 
 @pytest.mark.parametrize("prec", ["bf16x3", "bf16"])
 @pytest.mark.parametrize("n,part,Mu,Mp", [(16384, 127, 40, 33), (16385, 128, 40, 33), (17001, 129, 33, 255), (16513, 257, 65, 256),
-                                          (9000, 255, 257, 300), (33100, 33, 16, 130), (20000, 1, 2, 1)])
+                                          (9000, 255, 257, 300), (33100, 400, 16, 130), (13200, 150, 257, 600), (20000, 1, 2, 1)])
 def test_one_and_two_subtiles(prec, n, part, Mu, Mp):
     W, H = 500.0, 350.0
     wl = make_random(n, W, H, Mu, Mp, seed=n)
