@@ -130,7 +130,7 @@ def _blocks(x, y, w, h):
     for t in ts:
         if not isinstance(t, torch.Tensor) or t.dtype != torch.float64 or t.dim() != 1:
             raise TypeError("x, y, w, h must be 1-D float64 tensors")
-        if t.device != dev or t.shape[0] != n or not t.is_contiguous():
+        if t.device != dev or t.size(0) != n or not t.is_contiguous():
             raise ValueError("x, y, w, h must be contiguous, on one device, of equal length")
     if dev.type != "cuda":
         raise ValueError("x, y, w, h must live on a GPU (HIP) device")
@@ -138,11 +138,28 @@ def _blocks(x, y, w, h):
 
 
 def _vp(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
+
+
+# The current stream's handle without the Stream object around it (4 us of a call's 20), where torch has that entry.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    return torch.cuda.current_stream(dev).cuda_stream if _raw_stream is None else _raw_stream(dev.index)
+
+
+def _enqueue(name, dev, problem, *args):
+    """Call entry point `name` with the problem, the arguments and dev's current stream, dev being the current device
+    (made so only where it is not: the context manager takes another 4 us)."""
+    call = getattr(load(), name)
+    if dev.index is not None and torch.cuda.current_device() == dev.index:
+        st = call(ctypes.byref(problem), *args, _stream(dev))
+    else:
+        with torch.cuda.device(dev):
+            st = call(ctypes.byref(problem), *args, _stream(dev))
+    if st != PP_OK:
+        raise PPError(st, name)
 
 
 def _workspace(P, dev, workspace=None):
@@ -165,10 +182,7 @@ def coeffs(x, y, w, h, *, W, H, Mu, Mp, precision="fp64", basis="recompute", wor
     P = _problem(W, H, n, Mu, Mp, precision, basis)
     a = torch.empty((Mu, Mp), dtype=torch.float64, device=dev)
     ws, nb = _workspace(P, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_coeffs(ctypes.byref(P), _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_coeffs")
+    _enqueue("pp_coeffs", dev, P, _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(ws), nb)
     return a
 
 
@@ -179,11 +193,7 @@ def energy(x, y, w, h, *, W, H, Mu, Mp, precision="fp64", basis="recompute", wan
     E = torch.empty((), dtype=torch.float64, device=dev)
     a = torch.empty((Mu, Mp), dtype=torch.float64, device=dev) if want_coeffs else None
     ws, nb = _workspace(P, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_energy(ctypes.byref(P), _vp(x), _vp(y), _vp(w), _vp(h), _vp(E), _vp(a), _vp(ws), nb,
-                              _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_energy")
+    _enqueue("pp_energy", dev, P, _vp(x), _vp(y), _vp(w), _vp(h), _vp(E), _vp(a), _vp(ws), nb)
     return E, a
 
 
@@ -194,10 +204,7 @@ def energy_static(x, y, w, h, *, W, H, Mu, Mp, precision="fp64", want_coeffs=Tru
     P = _problem(W, H, n, Mu, Mp, precision, "recompute")
     E = torch.empty((), dtype=torch.float64, device=dev)
     a = torch.empty((Mu, Mp), dtype=torch.float64, device=dev) if want_coeffs else None
-    with torch.cuda.device(dev):
-        st = load().pp_energy_static(ctypes.byref(P), _vp(x), _vp(y), _vp(w), _vp(h), _vp(E), _vp(a), _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_energy_static")
+    _enqueue("pp_energy_static", dev, P, _vp(x), _vp(y), _vp(w), _vp(h), _vp(E), _vp(a))
     return E, a
 
 
@@ -218,11 +225,7 @@ def field(x, y, w, h, a, *, W, H, precision="fp64", basis="recompute", dE=None, 
     gx = torch.empty(n, dtype=torch.float64, device=dev)
     gy = torch.empty(n, dtype=torch.float64, device=dev)
     ws, nb = _workspace(P, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_field(ctypes.byref(P), _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(dE), _vp(gx), _vp(gy),
-                             _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_field")
+    _enqueue("pp_field", dev, P, _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(dE), _vp(gx), _vp(gy), _vp(ws), nb)
     return gx, gy
 
 
@@ -247,11 +250,8 @@ def point_field(px, py, a, *, W, H, precision="fp64", want=("psi", "xix", "xiy")
     outs = {k: (torch.empty(n, dtype=torch.float64, device=dev) if k in want else None)
             for k in ("psi", "xix", "xiy")}
     ws, nb = _workspace(P, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_point_field(ctypes.byref(P), _vp(px), _vp(py), _vp(a), _vp(outs["psi"]), _vp(outs["xix"]),
-                                   _vp(outs["xiy"]), _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_point_field")
+    _enqueue("pp_point_field", dev, P, _vp(px), _vp(py), _vp(a), _vp(outs["psi"]), _vp(outs["xix"]),
+             _vp(outs["xiy"]), _vp(ws), nb)
     return outs["psi"], outs["xix"], outs["xiy"]
 
 
@@ -262,11 +262,7 @@ def block_potential(x, y, w, h, a, *, W, H, precision="fp64", workspace=None):
     P = _problem(W, H, n, Mu, Mp, precision, "recompute")
     N = torch.empty(n, dtype=torch.float64, device=dev)
     ws, nb = _workspace(P, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_block_potential(ctypes.byref(P), _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(N), _vp(ws),
-                                       nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_block_potential")
+    _enqueue("pp_block_potential", dev, P, _vp(x), _vp(y), _vp(w), _vp(h), _vp(a), _vp(N), _vp(ws), nb)
     return N
 
 
@@ -310,11 +306,7 @@ def bin_density(x, y, w, h, *, W, H, m, workspace=None):
     B = _bin_problem(W, H, n, m, 1, 1)
     P = torch.empty((m, m), dtype=torch.float64, device=dev)
     ws, nb = _bin_ws(B, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_bin_density(ctypes.byref(B), _vp(x), _vp(y), _vp(w), _vp(h), _vp(P), _vp(ws), nb,
-                                   _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_bin_density")
+    _enqueue("pp_bin_density", dev, B, _vp(x), _vp(y), _vp(w), _vp(h), _vp(P), _vp(ws), nb)
     return P
 
 
@@ -327,10 +319,7 @@ def bin_coeffs(P, *, W, H, Mu, Mp, workspace=None):
     B = _bin_problem(W, H, 0, m, Mu, Mp)
     a = torch.empty((Mu, Mp), dtype=torch.float64, device=dev)
     ws, nb = _bin_ws(B, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_bin_coeffs(ctypes.byref(B), _vp(P), _vp(a), _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_bin_coeffs")
+    _enqueue("pp_bin_coeffs", dev, B, _vp(P), _vp(a), _vp(ws), nb)
     return a
 
 
@@ -346,11 +335,7 @@ def bin_field(a, *, W, H, m, want=("psi", "xix", "xiy"), workspace=None):
     outs = {k: (torch.empty((m, m), dtype=torch.float64, device=dev) if k in want else None)
             for k in ("psi", "xix", "xiy")}
     ws, nb = _bin_ws(B, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_bin_field(ctypes.byref(B), _vp(a), _vp(outs["psi"]), _vp(outs["xix"]), _vp(outs["xiy"]),
-                                 _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_bin_field")
+    _enqueue("pp_bin_field", dev, B, _vp(a), _vp(outs["psi"]), _vp(outs["xix"]), _vp(outs["xiy"]), _vp(ws), nb)
     return outs["psi"], outs["xix"], outs["xiy"]
 
 
@@ -369,11 +354,8 @@ def bin_interp(x, y, w, h, psi=None, xix=None, xiy=None, *, W, H, workspace=None
     B = _bin_problem(W, H, n, m, 1, 1)
     outs = [torch.empty(n, dtype=torch.float64, device=dev) if f is not None else None for f in fields]
     ws, nb = _bin_ws(B, dev, workspace)
-    with torch.cuda.device(dev):
-        st = load().pp_bin_interp(ctypes.byref(B), _vp(x), _vp(y), _vp(w), _vp(h), *[_vp(f) for f in fields],
-                                  *[_vp(o) for o in outs], _vp(ws), nb, _stream(dev))
-    if st != PP_OK:
-        raise PPError(st, "pp_bin_interp")
+    _enqueue("pp_bin_interp", dev, B, _vp(x), _vp(y), _vp(w), _vp(h), *[_vp(f) for f in fields],
+             *[_vp(o) for o in outs], _vp(ws), nb)
     return tuple(outs)
 
 
