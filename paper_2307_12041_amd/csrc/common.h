@@ -148,7 +148,7 @@ struct BwdAxisBf16 {
     const PhaseRec *ta;          // K-axis records (basis generated along K)
     const PhaseRec *te;          // epilogue-axis records (cosine differences)
     int Ka, Nb, Kh;              // K frequencies, N frequencies, K half length (multiple of 32)
-    const unsigned short *B;     // tiled operand (hi and lo bf16, see k_prep_bwd_bf16)
+    const unsigned short *B;     // tiled operand (hi and lo bf16, see prep_segment)
     double *gpart;               // out: [tiles_n][n]
     // Store mode (tab_h non-NULL): the K-axis basis read from its stored tables instead of
     // generated; tab_ld is their row length, tiles_b / tiles_n the grid of block / N tiles.

@@ -142,8 +142,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // ================================================================================================
 // Forward: At[u][p] = sum_i S_iu T_ip over a range of blocks.
-// Kernels: k_fwd1_bf16<X3> (one wave per SIMD, three products or one, further below) and the
-// store-mode k_fwd_bf16_st (512 threads = 8 waves, wave w owning the 128 x 64 output sub-tile (u-half
+// Kernels: k_fwd1_bf16<X3> (one wave per SIMD, three products or one, further below), k_fwd_sum_bf16<X3> (short
+// splits, added on the way) and the store-mode k_fwd_bf16_st (512 threads = 8 waves, wave w owning the 128 x 64 output sub-tile (u-half
 // w / 4, p-quarter w % 4), contracting tiles staged from the stored tables with fwd_mma).
 // LDS tile layout: [block][frequency] bf16, 512-byte rows with XOR-swizzled 16-byte segments;
 // MFMA operands are read with the transpose read.
