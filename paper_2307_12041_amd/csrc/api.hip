@@ -79,7 +79,7 @@ int validate_blocks(const pp_problem *P, const double *x, const double *y, const
 // 100,000 314 and 200; 200,000 470 and 376; 400,000 713 and 766.  One product: 130 and 43; 263 and 139; 350 and 254; 494 and 469.)
 // The sums of groups of splits take at most half the splits' partials in bytes, so they fit where those lie.
 void plan_split_sums(const pp_problem &P, FwdPlan &pl) {
-    const bool x3 = P.precision == PP_BF16X3;
+    const bool x3 = P.precision != PP_BF16;
     const double c128 = x3 ? 0.92 : 0.53, c256 = x3 ? 2.45 : 1.15, per_byte = 1.0 / 2.7e6, cps = (double)pl.chunks_per_split;
     const double MM = (double)P.Mu * (double)P.Mp;
     const int64_t tiles256 = (int64_t)pl.tiles_u * pl.tiles_p;
@@ -132,7 +132,10 @@ FwdPlan fwd_plan(const pp_problem &P) {
     pl.splits = (int)((pl.chunks + pl.chunks_per_split - 1) / pl.chunks_per_split);
     if (pl.splits < 1) pl.splits = 1;
     pl.part_elem = P.precision == PP_FP64 ? 8 : 4;
-    if ((P.precision == PP_BF16X3 || P.precision == PP_BF16) && P.basis_mode != PP_BASIS_STORE && pl.splits >= 2)
+    // (The mixed split too where its three-product corner is the whole plane.)
+    const bool whole = mix_tiles(P.Mu) == pl.tiles_u && mix_tiles(P.Mp) == pl.tiles_p;
+    if ((P.precision == PP_BF16X3 || P.precision == PP_BF16 || (P.precision == PP_BF16MIX && whole)) &&
+        P.basis_mode != PP_BASIS_STORE && pl.splits >= 2)
         plan_split_sums(P, pl);
     return pl;
 }
@@ -319,13 +322,13 @@ int run_forward(const pp_problem &P, const double *x, const double *y, const dou
         } else if (is_fp8(P.precision)) {
             TimedLaunch t(T("fwd"), s);
             err = launch_fwd_fp8(f, x3, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (float *)part, s);
+        } else if (f.groups) {
+            TimedLaunch t(T("fwd"), s);
+            err = launch_fwd_sum_bf16(f, P.precision != PP_BF16, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (double *)part, s);
         } else if (P.precision == PP_BF16MIX) {
             TimedLaunch t(T("fwd"), s);
             err = launch_fwd_bf16_mix(f, mix_tiles(P.Mu), mix_tiles(P.Mp), P.n, P.Mu, P.Mp, tx, ty, sx, sy,
                                       (float *)part, s);
-        } else if (f.groups) {
-            TimedLaunch t(T("fwd"), s);
-            err = launch_fwd_sum_bf16(f, x3, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (double *)part, s);
         } else {
             TimedLaunch t(T("fwd"), s);
             err = launch_fwd_bf16(f, x3, P.n, P.Mu, P.Mp, tx, ty, sx, sy, (float *)part, s);

@@ -36,3 +36,12 @@ def test_groups_of_splits(prec, n, Mu, Mp):
     assert np.linalg.norm(a - as_) <= 1e-12 * np.linalg.norm(as_)
     assert np.linalg.norm(a - ao) <= TOL[prec] * np.linalg.norm(ao)
     assert abs(float(E) - Eo) <= 2 * TOL[prec] * abs(Eo)
+
+
+@pytest.mark.parametrize("n,Mu,Mp", [(65, 128, 129), (997, 256, 40), (70001, 33, 256)])
+def test_mixed_split_of_one_tile_per_axis(n, Mu, Mp):
+    """Up to 256 frequencies per axis the mixed split contracts everything with three products: bf16x3's coefficients."""
+    wl = make_random(n, 500.0, 300.0, Mu, Mp, seed=n)
+    x, y, w, h = (torch.as_tensor(np.ascontiguousarray(v), device="cuda:0") for v in wl.arrays())
+    size = dict(W=wl.W, H=wl.H, Mu=Mu, Mp=Mp)
+    assert torch.equal(pp.coeffs(x, y, w, h, precision="bf16mix", **size), pp.coeffs(x, y, w, h, precision="bf16x3", **size))
