@@ -24,6 +24,7 @@
 // differences as -2 sin(k a) sin(k b) with a = pi c / L, b = pi size / (2L) for centre c (no cancellation for narrow blocks).
 #include <type_traits>
 
+#include "basis_gen.h"
 #include "common.h"
 
 namespace pp {
@@ -48,7 +49,8 @@ template <> struct Mat<float> {
 
 // sin(pi t) and cos(pi t), |t| < 2^50: t = q / 2 + f exactly with an integer q (its low bits are read off the sum that
 // rounds it) and |f| <= 1/4, then the Taylor polynomials of sin(pi f) and cos(pi f) (coefficients pi^j / j!, rounded; the first
-// term left out is below 2^-58 of the result).  An infinite or NaN t gives NaN.
+// term left out is below 2^-58 of the result).  An infinite or NaN t gives NaN.  The callers' t is a frequency (at most 2^16) times
+// a phase reduced by whole turns, so that it stays in that range however far outside the region a block lies.
 __device__ __forceinline__ void sincospi_seed64(double t, double &s, double &c) {
     const double magic = 6755399441055744.0;   // 1.5 * 2^52
     const double d = fma(2.0, t, magic);
@@ -111,7 +113,7 @@ struct BlockRuns {
     // Every thread of the workgroup calls this; ph: LDS for 4 phasors per block; i: the block's index of `blocks`.
     template <int GROUPS, int BLOCKS>
     __device__ __forceinline__ void init(double c, double sz, double L, int k0, int J, double2 *ph, int i, int group) {
-        const double ta = c / L, tb = 0.5 * sz / L;
+        const double ta = gen::reduce_half_turns(c / L), tb = gen::reduce_half_turns(0.5 * sz / L);
         size = sz;
         pa.set((double)k0 * ta);
         if constexpr (kSize) pb.set((double)k0 * tb);
@@ -214,7 +216,6 @@ __global__ __launch_bounds__(256, TILE == 256 ? 1 : 2) void k_fwd_mat(int64_t n,
 
     const bool side_y = tid >= 128;
     const int kb = tid & 31, run = (tid >> 5) & 3;
-    const double *__restrict__ cc = side_y ? y : x, *__restrict__ ss = side_y ? h : w;
     const double L = side_y ? H : W;
     const int f0 = (side_y ? tp0 : tu0) + run * R;
     T *dst = (side_y ? Ys : Xs) + kb * LD + run * R;
@@ -225,22 +226,26 @@ __global__ __launch_bounds__(256, TILE == 256 ? 1 : 2) void k_fwd_mat(int64_t n,
 #pragma unroll
         for (int b = 0; b < S; ++b) acc[a][b] = v4{(T)0, (T)0, (T)0, (T)0};
 
-    // block data are requested a chunk ahead; past the last block: an absent one (size 0)
-    auto fetch = [&](int64_t c, double &pc, double &ps) {
+    // Block data are requested a chunk ahead, centres by the lower half of a wave and sizes by the upper one; past the last block:
+    // an absent one (size 0).  Each half divides and reduces its own phase, a = pi c / L or b = pi size / (2L).
+    const double *__restrict__ src = side_y ? (lane < 32 ? y : h) : (lane < 32 ? x : w);
+    const double period = lane < 32 ? L : 2.0 * L;
+    auto fetch = [&](int64_t c) {
         const int64_t ib = c * kK + kb;
         const bool in = ib < n;
-        pc = cc[in ? ib : 0];
-        ps = ss[in ? ib : 0];
-        if (!in) pc = ps = 0.0;
+        const double v = src[in ? ib : 0];
+        return in ? v : 0.0;
     };
-    double pc = 0.0, ps = 0.0;
-    if (c_begin < c_end) fetch(c_begin, pc, ps);
+    double pv = c_begin < c_end ? fetch(c_begin) : 0.0;
     for (int64_t c = c_begin; c < c_end; ++c) {
-        const double ta = pc / L, tb = 0.5 * ps / L, sz = ps;
-        if (c + 1 < c_end) fetch(c + 1, pc, ps);
+        const double t = gen::reduce_half_turns(pv / period);
+        double ctr, sz, ta, tb;
+        both_halves(pv, ctr, sz);
+        both_halves(t, ta, tb);
+        if (c + 1 < c_end) pv = fetch(c + 1);
         __builtin_amdgcn_s_setprio(3);
         Phasor own, step_a, step_b;
-        own.set(lane < 32 ? ta : tb);
+        own.set(t);
         both_halves(own.c, step_a.c, step_b.c);
         both_halves(own.s, step_a.s, step_b.s);
         lds_barrier();   // the previous chunk has been contracted
