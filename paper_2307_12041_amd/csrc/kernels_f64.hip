@@ -345,16 +345,17 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis>
     const int64_t ib = ib0 + gi;
     const bool valid = ib < n;
 
-    // Copies of the KH rows from k on into buffer h: wave w copies rows w, w + 4, ..; a row past Ka is the last row again
-    // (its basis values are zero), and columns past Nb hold whatever follows in B, within the buffer's bounds (the
-    // accumulators of such columns are cleared before the epilogue).
+    // Copies of the KH rows from k on into buffer h: wave w copies rows w, w + 4, ..; a row past Ka is a copy of no bytes, which
+    // writes zeros (its basis values are zero too, and zero times an infinite coefficient of some other row would be NaN), and
+    // columns past Nb hold whatever follows in B, within the buffer's bounds (the accumulators of such columns are cleared
+    // before the epilogue).
     typedef __attribute__((address_space(3))) void lds_void;
     auto copy_half = [&](int k, int h) {
 #pragma unroll
         for (int q = 0; q < KH / 4; ++q) {
             const int row = 4 * q + wave;
             const int64_t at = (int64_t)min(k + row, ax.Ka - 1) * ax.Nb + n0;
-            const int64_t left = ((int64_t)ax.Ka * ax.Nb - at) * (int64_t)sizeof(T);
+            const int64_t left = k + row < ax.Ka ? ((int64_t)ax.Ka * ax.Nb - at) * (int64_t)sizeof(T) : 0;
             const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)((const T *)ax.B + at), (short)0, (int)min(left, (int64_t)TN * (int64_t)sizeof(T)), 0x00020000);
             char *dst = smem + BYTES_A + (h * KH + row) * LN * (int)sizeof(T);
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void k_bwd_mat(int64_t n, AxisPair<BwdAxis>
         const int ka = k0 + group * RA;
         T *dst = As + (group * RA) * LB + gi;
         runs.template gen<RA>(ka, 0.0, dst, LB);
-        if (k0 + kK > ax.Ka) {   // the last chunk's rows past Ka meet finite operand values: no basis there
+        if (k0 + kK > ax.Ka) {   // the last chunk: no basis past Ka
 #pragma unroll
             for (int k = 0; k < RA; ++k)
                 if (ka + k >= ax.Ka) dst[k * LB] = (T)0;
