@@ -363,8 +363,9 @@ BinLayout bin_layout(const pp_bin_problem &B) {
     BinLayout L{};
     const size_t m = (size_t)B.m;
     const size_t t1 = m * (size_t)B.Mp, t2 = 2 * (size_t)B.Mu * m;
+    const size_t fft = bin_fft_table_doubles(bin_fft_plan(B.m)), products = 8 * m;   // (8 m is the larger one from m = 3 on)
     L.tab = 0;
-    L.tmp = align256(8 * m * sizeof(double));
+    L.tmp = align256((fft > products ? fft : products) * sizeof(double));
     L.list = L.tmp + align256((t1 > t2 ? t1 : t2) * sizeof(double));
     L.total = L.list + align256(((size_t)(B.n > 0 ? B.n : 0) + 1) * sizeof(int));
     return L;

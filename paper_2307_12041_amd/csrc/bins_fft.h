@@ -16,9 +16,26 @@ struct BinFft {
     bool chirp;          // Bluestein's form
 };
 
-BinFft bin_fft_plan(int m);
+inline BinFft bin_fft_plan(int m) {
+    BinFft f{m, 0, false};
+    if (m >= 64 && m <= 8192 && (m & (m - 1)) == 0) {
+        f.L = m;
+    } else if (m <= 4096) {
+        f.chirp = true;
+        f.L = 8;
+        while (f.L < 2 * m - 1) f.L *= 2;
+    }
+    return f;
+}
 
-// Fills the device tables (8 m doubles: twiddles, phases, the chirp's transform) that the transforms read.
+// Doubles of the device tables.  L = m: m phases and m twiddles, complex.  Bluestein's form: m phases, L / 4 twiddles and L / 2 + 1
+// points of the chirp's transform, at most 8 m doubles from m = 3 on (L <= 4 m - 4), 16 and 18 at m = 1 and 2 (L = 8).
+inline size_t bin_fft_table_doubles(const BinFft &f) {
+    if (!f.chirp) return 4 * (size_t)f.m;
+    return 2 * ((size_t)f.m + (size_t)f.L / 4 + (size_t)f.L / 2 + 1);
+}
+
+// Fills the device tables (bin_fft_table_doubles: phases, twiddles, the chirp's transform) that the transforms read.
 hipError_t launch_bin_fft_tables(const BinFft &f, double *tab, hipStream_t s);
 
 // Coefficients: Q[l][p] = sum_j P[l][j] C_p(j) (Q: m x Mp scratch), then

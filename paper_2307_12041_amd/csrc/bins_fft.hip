@@ -35,7 +35,7 @@ __device__ __forceinline__ cplx cmul(cplx a, cplx b) { return cplx{a.x * b.x - a
 __device__ __forceinline__ cplx swapped(cplx a) { return cplx{a.y, a.x}; }
 __device__ __forceinline__ cplx times_minus_i(cplx a) { return cplx{a.y, -a.x}; }
 
-// Device tables, 8 N doubles at most (L < 4 N - 2):
+// Device tables (bin_fft_table_doubles of them):
 //   T[k] = e^{i pi k / 2N}, k < N;
 //   W[k] = e^{-2 pi i k / L}: k < L where L = N, one quadrant (k < L / 4) in Bluestein's form, which also has
 //   Bh[k] = DFT_L(b) / L, k <= L / 2 (b is even, so Bh[L - k] = Bh[k]).
@@ -390,18 +390,6 @@ hipError_t launch_points(const BinFft &f, FftArgs A, int count, int jobs, hipStr
 }
 
 }  // namespace
-
-BinFft bin_fft_plan(int m) {
-    BinFft f{m, 0, false};
-    if (m >= 64 && m <= 8192 && (m & (m - 1)) == 0) {
-        f.L = m;
-    } else if (m <= 4096) {
-        f.chirp = true;
-        f.L = 8;
-        while (f.L < 2 * m - 1) f.L *= 2;
-    }
-    return f;
-}
 
 hipError_t launch_bin_fft_tables(const BinFft &f, double *tab, hipStream_t s) {
     const Tables t = tables(f, tab);
