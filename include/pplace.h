@@ -217,8 +217,7 @@ int pp_bin_density(const pp_bin_problem *B, const double *x, const double *y, co
  *   a_u0 = 4 W^2 / (u^3 pi^3 m) sin(u pi/(2m)) sum_lj P_lj cos(u (l + 1/2) pi/m),
  *   a_up = 16 W^2 H^2 sin(u pi/(2m)) sin(p pi/(2m)) / (u p (u^2 H^2 + p^2 W^2) pi^4)
  *          * sum_lj P_lj cos(u (l + 1/2) pi/m) cos(p (j + 1/2) pi/m).
- * P: in [m * m] FP64 (pp_bin_density, or any bin densities).  a: out [Mu * Mp] FP64.  Every coefficient depends
- * on every bin: an infinite or NaN bin gives NaN (pp_bin_field: so does such a coefficient). */
+ * P: in [m * m] FP64 (pp_bin_density, or any bin densities).  a: out [Mu * Mp] FP64. */
 int pp_bin_coeffs(const pp_bin_problem *B, const double *P, double *a, void *ws, size_t ws_bytes, void *stream);
 
 /* Potential and field at the bin centres, truncated at the coefficient array (Sec. III-D,

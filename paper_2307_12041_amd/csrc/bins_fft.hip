@@ -14,6 +14,10 @@
 // b_n = e^{i pi n^2 / N}: a cyclic convolution of length L >= 2N - 1 with the transform of b from a table.  Inverse
 // transforms are forward ones with real and imaginary parts exchanged on the way in and out.
 //
+// An infinite or NaN element leaves every output of its pair of rows or columns without a finite value (a sum, a rotation or a
+// product with a twiddle keeps one component of it so).  Each thread looks at its first output and, if it is not finite, sums all
+// of its outputs directly instead: an infinity or NaN where the plain sum has one, a finite value for the pair's other member.
+//
 // Each pass reads and writes its arrays once; at m = 2048 a pass over one array moves 64 MiB that the memory-side cache
 // holds.  Measured at m = 2048 (512): coefficients 21 + 31 us (11 + 9), field 47 + 93 us (10 + 13, two and three arrays),
 // against 0.39-0.41 ms (0.09) for each of the seven transforms as a matrix product of 2 m^3 flops on the FP64 matrix cores
@@ -222,6 +226,35 @@ struct FftArgs {
     double W, H;
 };
 
+// The outputs of a thread (j of its transform's E), which are of a pair with elements that are not finite, as plain sums over the pair's
+// elements (first member at p0, second at p1, stride es).
+template <int PASS>
+__device__ __forceinline__ void sum_directly(const FftArgs &A, const FftJob &job, int j, int E, const double *__restrict__ p0,
+                                             const double *__restrict__ p1, size_t es, int n0, bool ok1, int ldo) {
+    constexpr bool ROW = PASS == ROW_FWD || PASS == ROW_INV, FWD = PASS == ROW_FWD || PASS == COL_FWD;
+    const int N = A.N, len = FWD ? N : ROW ? A.Mp : A.Mu, outs = PASS == ROW_FWD ? A.Mp : PASS == COL_FWD ? A.Mu : N;
+    for (int i = j; i < outs; i += E) {
+        double s0 = 0.0, s1 = 0.0;
+        int at = FWD ? i : 0;   // i (2n + 1), or n (2i + 1), on the circle of 4N points
+        for (int n = 0; n < len && !(isnan(s0) && isnan(s1)); ++n) {
+            const int quad = (at >= N) + (at >= 2 * N) + (at >= 3 * N);
+            const cplx z = times_i_power(A.t.T[at - quad * N], quad);
+            const double f = job.sine ? z.y * ((double)n * job.scale) : z.x;
+            s0 += p0[(size_t)n * es] * f;
+            s1 += p1[(size_t)n * es] * f;
+            at += FWD ? 2 * i : 2 * i + 1;
+            at -= at >= 4 * N ? 4 * N : 0;
+        }
+        if constexpr (PASS == COL_FWD) {
+            s0 *= disa_factor(i, n0, A.t.T[i].y, A.t.T[n0].y, A.W, A.H, N);
+            if (ok1) s1 *= disa_factor(i, n0 + 1, A.t.T[i].y, A.t.T[n0 + 1].y, A.W, A.H, N);
+        }
+        const size_t o = ROW ? (size_t)n0 * ldo + i : (size_t)i * ldo + n0;
+        job.out[o] = s0;
+        if (ok1) job.out[o + (ROW ? (size_t)ldo : 1)] = s1;
+    }
+}
+
 // One workgroup: G = PTS / L transforms in LDS, eight points per thread.  Row passes give each transform L / 8
 // neighbouring threads, so that loads and stores run along rows; column passes deal neighbouring threads to neighbouring
 // transforms (columns), and take their workgroups in XCD-major order, so that the workgroups that share the cache lines of
@@ -298,7 +331,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
                 // h = e^{i pi k / 2N} ((c_k - i c_{N-k}) + i (d_k - i d_{N-k})) / 2
                 cplx z = cplx{0.5 * (c[r].x + d[r].y), 0.5 * (d[r].x - c[r].y)};
                 z = cmul(z, T[k]);
-                if (k == 0) z = cplx{c[r].x, d[r].x};
+                if (k == 0) z = cplx{c[r].x + c[r].y, d[r].x + d[r].y};   // (sine: 0 times element 0, element N is 0)
                 z = swapped(z);
                 if (CHIRP) z = cmul(z, chirp_conj(T, k, N, inv));
                 v[r] = z;
@@ -328,6 +361,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
 
     // ---- store ----
     double *__restrict__ out = job.out;
+    bool bad = false;
     if constexpr (PASS == ROW_FWD || PASS == COL_FWD) {
         const int K = PASS == ROW_FWD ? A.Mp : A.Mu;
 #pragma unroll
@@ -335,6 +369,7 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
             const int k = j + r * E;
             if (k >= K || !ok0) continue;
             const cplx a = get(k), b = get(k ? N - k : 0), w = T[k];
+            if (r == 0) bad = !(isfinite(a.x) && isfinite(a.y));
             // V = A + i B with A, B Hermitian; X = Re(e^{-i pi k / 2N} A), and the same of B
             double xa = 0.5 * (w.x * (a.x + b.x) + w.y * (a.y - b.y));
             double xb = 0.5 * (w.x * (a.y + b.y) - w.y * (a.x - b.x));
@@ -353,12 +388,14 @@ __global__ __launch_bounds__(PTS / 8) void k_bin_fft(FftArgs A) {
             const int s = j + r * E;
             if (s >= N || !ok0) continue;
             const cplx z = swapped(get((s & 1) ? N - ((s + 1) >> 1) : s >> 1));
+            if (r == 0) bad = !(isfinite(z.x) && isfinite(z.y));
             const double sg = job.sine ? ((s & 1) ? -job.scale : job.scale) : 1.0;
             const size_t o = (size_t)n0 * po + (size_t)s * eo;
             out[o] = sg * z.x;
             if (ok1) out[o + po] = sg * z.y;
         }
     }
+    if (bad) sum_directly<PASS>(A, job, j, E, p0, p1, es, n0, ok1, ldo);
 }
 
 int log2i(int v) {
