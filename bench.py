@@ -229,8 +229,6 @@ def timed_steps(pp, torch, t, wl, prec, steps, warmup, ws, positions=None, basis
     stages = {}
     for st in ("tables", "seeds", "build", "fwd", "reduce", "energy", "prep", "bwd", "final", "point", "potential"):
         ms, cnt = pp.timing_query(st)
-        if st == "bwd":
-            cnt *= 2   # one record for the gx and gy contractions of a step; figures below are per contraction
         if cnt:
             stages[st] = (ms, cnt)
     pp.timing_enable(False)

@@ -256,12 +256,15 @@ const char *pp_strerror(int status);
  * call first discards all earlier records and their events.
  * pp_timing_query(name, &ms, &count) waits for the recorded events of one stage and returns their
  * summed duration in milliseconds and the number of records.  Stage names: "tables" (per-block
- * phase records, and the run seeds of a forward), "fwd" (coefficient contraction), "reduce" (split-K sum, scale, energy
- * partials), "energy" (final energy sum), "prep" (row-form operands; bf16 types: and the phase records), "bwd" (the two
- * gradient contractions, one record for both), "final" (per-block partial sums), "build" (store-mode basis
+ * phase records), "seeds" (run seeds of the bf16 and FP8 forwards), "fwd" (coefficient contraction), "reduce" (split-K sum,
+ * scale, energy partials), "energy" (final energy sum), "prep" (row-form operands), "bwd" (the two gradient
+ * contractions, one record each), "final" (per-block partial sums; one record a call), "build" (store-mode basis
  * tables), "point" (pp_point_field
  * contractions), "potential" (pp_block_potential contraction), "bin_density", "bin_coeffs",
- * "bin_field", "bin_interp" (the bin scheme, all launches of one call in one record).  Unknown names give count 0.
+ * "bin_field", "bin_interp" (the bin scheme, all launches of one call in one record).  A stage that the launch of another one
+ * does has its records there without time: "seeds" is in the time of "tables", the "tables" of a bf16 gradient or evaluation in
+ * that of "prep", the "final" of results that a contraction writes itself in the contraction's; both gradient contractions
+ * share one launch's time.  Unknown names give count 0.
  * Returns PP_OK, PP_ERR_ARG for NULL arguments, PP_ERR_DEVICE if an event query fails.  Recording
  * is process wide and guarded by a lock; it is meant for benchmarks, not for production calls. */
 int pp_timing_enable(int on);

@@ -307,6 +307,7 @@ int run_forward(const pp_problem &P, const double *x, const double *y, const dou
             err = launch_axis_tables(P.n, AxisTables{x, w, P.W, tx, sx, seed_runs(P.Mu)},
                                      AxisTables{y, h, P.H, ty, sy, seed_runs(P.Mp)}, s);
         }
+        count_stage(T("seeds"));
         if (err != hipSuccess) return PP_ERR_DEVICE;
         if (P.basis_mode == PP_BASIS_STORE) {
             const StoreTables st = store_tables(P, L, base);
@@ -401,12 +402,13 @@ RowOut row_out(bool direct, int tiles_n, double *r, double *r2, const double *dE
     return direct && tiles_n == 1 ? RowOut{r, r2, dE} : RowOut{nullptr, nullptr, nullptr};
 }
 
+// (The one record of this stage in a call is counted by the caller: there may be two launches, or none.)
 hipError_t sum_partials(bool direct, const double *gpx, int tx, double *gx, const double *gpy, int ty, double *gy,
                         int64_t n, const double *dE, hipStream_t s) {
     if (direct && tx == 1) gx = nullptr;
     if (direct && ty == 1) gy = nullptr;
     if (!gx && !gy) return hipSuccess;
-    TimedLaunch t("final", s);
+    TimedLaunch t("final", s, 0);
     return launch_bwd_final(gpx, tx, gpy, ty, n, dE, gx, gy, s);
 }
 
@@ -503,7 +505,7 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
         // gx: K = p (basis of y), epilogue over u (x);  gy: K = u (basis of x), epilogue over p (y).
         const BwdAxisFp8 axx{ty, tx, P->Mp, P->Mu, khx, bxt, b0x, gpx, nullptr, 0.0f};
         const BwdAxisFp8 axy{tx, ty, P->Mu, P->Mp, khy, byt, b0y, gpy, nullptr, 0.0f};
-        TimedLaunch t("bwd", s);
+        TimedLaunch t("bwd", s, 2);
         if (launch_bwd_fp8(ROW_FIELD, x3, P->n, axx, s) != hipSuccess ||
             launch_bwd_fp8(ROW_FIELD, x3, P->n, axy, s) != hipSuccess)
             return PP_ERR_DEVICE;
@@ -513,6 +515,7 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
         unsigned short *bxt = (unsigned short *)(base + L.bx), *byt = (unsigned short *)(base + L.by);
         const int khx = bf16_kh(P->Mp), khy = bf16_kh(P->Mu);
         {
+            count_stage("tables");
             TimedLaunch t("prep", s);
             if (launch_setup_bf16(P->n, AxisTables{x, w, P->W, tx, nullptr, 0}, AxisTables{y, h, P->H, ty, nullptr, 0},
                                   ROW_FIELD, a, P->Mu, P->Mp, P->W, P->H,
@@ -531,7 +534,7 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
             axy.tab_h = st.xh; axy.tab_l = st.xl; axy.tab_ld = st.ldx;
             axy.tiles_b = tb; axy.tiles_n = (P->Mp + 255) / 256;
         }
-        TimedLaunch t("bwd", s);
+        TimedLaunch t("bwd", s, 2);
         if (P->precision == PP_BF16MIX) {
             // the low-frequency N tiles with three products, the others with one (the K axis whole in
             // both); each launch writes the partial row sums of its own N tiles
@@ -556,9 +559,10 @@ int pp_field(const pp_problem *P, const double *x, const double *y, const double
         BwdAxis axx{y, h, P->H, P->Mp, x, w, P->W, P->Mu, bx, gpx, nullptr, ox};
         // gy: K = u (basis of x), epilogue over p (cosine differences of y), operand By[u][p].
         BwdAxis axy{x, w, P->W, P->Mu, y, h, P->H, P->Mp, by, gpy, nullptr, oy};
-        TimedLaunch t("bwd", s);
+        TimedLaunch t("bwd", s, 2);
         if (rowform(*P, ROW_FIELD, b, axx, &axy, s) != hipSuccess) return PP_ERR_DEVICE;
     }
+    count_stage("final");
     return sum_partials(direct, gpx, b.tiles_nx, gx, gpy, b.tiles_ny, gy, P->n, dE, s) == hipSuccess ? PP_OK : PP_ERR_DEVICE;
 }
 
@@ -593,6 +597,7 @@ int pp_point_field(const pp_problem *P, const double *px, const double *py, cons
         unsigned short *bxt = (unsigned short *)bx, *byt = (unsigned short *)by;
         const int khx = bf16_kh(P->Mp), khy = bf16_kh(P->Mu);
         {
+            count_stage("tables");
             TimedLaunch t("prep", s);
             if (launch_setup_bf16(P->n, AxisTables{px, nullptr, P->W, tx, nullptr, 0},
                                   AxisTables{py, nullptr, P->H, ty, nullptr, 0}, ROW_POINT_DUAL, a, P->Mu, P->Mp, P->W,
@@ -625,6 +630,7 @@ int pp_point_field(const pp_problem *P, const double *px, const double *py, cons
             if (rowform(*P, ROW_POINT_WSIN, b, axy, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
         }
     }
+    count_stage("final");
     if (sum_partials(direct, gp1, b.tiles_nx, psi, gpy, b.tiles_ny, xiy, P->n, nullptr, s) != hipSuccess ||
         sum_partials(direct, gp2, b.tiles_nx, xix, nullptr, 0, nullptr, P->n, nullptr, s) != hipSuccess)
         return PP_ERR_DEVICE;
@@ -657,6 +663,7 @@ int pp_block_potential(const pp_problem *P, const double *x, const double *y, co
         unsigned short *bxt = (unsigned short *)bx;
         const int khx = bf16_kh(P->Mp);
         {
+            count_stage("tables");
             TimedLaunch t("prep", s);
             if (launch_setup_bf16(P->n, AxisTables{x, w, P->W, tx, nullptr, 0}, AxisTables{y, h, P->H, ty, nullptr, 0},
                                   ROW_POTENTIAL, a, P->Mu, P->Mp, P->W, P->H,
@@ -672,6 +679,7 @@ int pp_block_potential(const pp_problem *P, const double *x, const double *y, co
         TimedLaunch t("potential", s);
         if (rowform(*P, ROW_POTENTIAL, b, ax, nullptr, s) != hipSuccess) return PP_ERR_DEVICE;
     }
+    count_stage("final");
     return sum_partials(direct, gp, b.tiles_nx, N, nullptr, 0, nullptr, P->n, nullptr, s) == hipSuccess ? PP_OK
                                                                                                        : PP_ERR_DEVICE;
 }

@@ -198,18 +198,22 @@ struct StoreTables {
     int ldx, ldy;
 };
 
-// Brackets one kernel launch with HIP events when event timing is on (timing.hip); a NULL name
+// Brackets one kernel launch with HIP events when event timing is on (timing.hip), as `count` records of its stage; a NULL name
 // marks a launch that is never timed (no event is created for it).
 class TimedLaunch {
   public:
-    TimedLaunch(const char *name, hipStream_t s);
+    TimedLaunch(const char *name, hipStream_t s, int count = 1);
     ~TimedLaunch();
   private:
     const char *name_;
     hipStream_t s_;
+    int count_;
     void *start_ = nullptr, *stop_ = nullptr;
     bool active_ = false;
 };
+
+// A record without time, for a stage that the launch of another one does (a caller who divides by its count finds it there).
+void count_stage(const char *name);
 
 // ---- launchers (each defined next to its kernels) ----
 hipError_t launch_fwd_f64(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W, double H,

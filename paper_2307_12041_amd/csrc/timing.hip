@@ -13,7 +13,8 @@ namespace {
 
 struct Rec {
     const char *name;
-    hipEvent_t start, stop;
+    hipEvent_t start, stop;   // null: a stage that another stage's launch does
+    int count;
 };
 
 std::mutex g_mu;
@@ -22,6 +23,7 @@ std::vector<Rec> g_recs;
 
 void clear_locked() {
     for (Rec &r : g_recs) {
+        if (!r.start) continue;
         (void)hipEventDestroy(r.start);
         (void)hipEventDestroy(r.stop);
     }
@@ -30,7 +32,7 @@ void clear_locked() {
 
 }  // namespace
 
-TimedLaunch::TimedLaunch(const char *name, hipStream_t s) : name_(name), s_(s) {
+TimedLaunch::TimedLaunch(const char *name, hipStream_t s, int count) : name_(name), s_(s), count_(count) {
     if (!name) return;   // an untimed launch site
     std::lock_guard<std::mutex> lk(g_mu);
     if (!g_on) return;
@@ -48,7 +50,13 @@ TimedLaunch::~TimedLaunch() {
     if (!active_) return;
     (void)hipEventRecord((hipEvent_t)stop_, s_);
     std::lock_guard<std::mutex> lk(g_mu);
-    g_recs.push_back(Rec{name_, (hipEvent_t)start_, (hipEvent_t)stop_});
+    g_recs.push_back(Rec{name_, (hipEvent_t)start_, (hipEvent_t)stop_, count_});
+}
+
+void count_stage(const char *name) {
+    if (!name) return;
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (g_on) g_recs.push_back(Rec{name, nullptr, nullptr, 1});
 }
 
 }  // namespace pp
@@ -71,11 +79,12 @@ int pp_timing_query(const char *name, double *total_ms, int *count) {
     int c = 0;
     for (const Rec &r : g_recs) {
         if (strcmp(r.name, name) != 0) continue;
+        c += r.count;
+        if (!r.start) continue;
         if (hipEventSynchronize(r.stop) != hipSuccess) return PP_ERR_DEVICE;
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, r.start, r.stop) != hipSuccess) return PP_ERR_DEVICE;
         tot += ms;
-        ++c;
     }
     *total_ms = tot;
     *count = c;
