@@ -1744,19 +1744,25 @@ __device__ __forceinline__ void bwd1_rows(char *smem, int64_t n, const BwdAxisBf
 
 // X3: three products per pair (hi*hi, lo*hi, hi*lo); otherwise one (hi*hi).  A grid of (nb2 + nb1, N tiles), the first nb2
 // N tiles of its workgroups taking 256 blocks each, the rest 128 of the blocks after those; workgroups that follow
-// each other share an N tile.
+// each other share an N tile.  Where the first contraction's K loop is more than twice the second's, the smaller workgroups of the
+// first come before the second contraction, so that no long ones are left for the end.
 template <bool X3, int KA, int E1, int E2>
 __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf16> P, unsigned nb2, unsigned nb1) {
     __shared__ __attribute__((aligned(16))) char smem[2 * BBUF];
     bool two = nb1 == 0;
     unsigned t = blockIdx.y, b = blockIdx.x;
     if (nb1 != 0 && nb2 != 0) {
-        unsigned w = blockIdx.y * gridDim.x + blockIdx.x;
-        const unsigned first = nb2 * gridDim.y;
+        unsigned w = blockIdx.y * gridDim.x + blockIdx.x, tiles = gridDim.y, t0 = 0;
+        if (P.a[0].Ka > 2 * P.a[1].Ka) {
+            const unsigned own = gridDim.x * (unsigned)P.tiles0;
+            if (w < own) tiles = (unsigned)P.tiles0;
+            else w -= own, tiles -= (unsigned)P.tiles0, t0 = (unsigned)P.tiles0;
+        }
+        const unsigned first = nb2 * tiles;
         two = w < first;
         if (!two) w -= first;
         const unsigned nb = two ? nb2 : nb1;
-        t = w / nb;
+        t = t0 + w / nb;
         b = w % nb;
     }
     const bool second = (int)t >= P.tiles0;
@@ -2024,6 +2030,7 @@ namespace {
 template <int KA, int E1, int E2>
 hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax0, const BwdAxisBf16 *ax1, hipStream_t s) {
     AxisPair<BwdAxisBf16> P{{ax0, ax1 ? *ax1 : ax0}, 0};
+    if (ax1 && ax1->Ka > ax0.Ka) std::swap(P.a[0], P.a[1]);   // (see AxisPair)
     int tiles[2] = {0, 0};
     for (int k = 0; k < (ax1 ? 2 : 1); ++k) {
         const BwdAxisBf16 &ax = P.a[k];
