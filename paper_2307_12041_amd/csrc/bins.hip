@@ -349,6 +349,21 @@ hipError_t gemm(int M, int N, int K, const BinOp &A, const BinOp &B, const doubl
     return hipGetLastError();
 }
 
+// Estimated time in us of one product, fitted like bin_fft_field_us (5 %): a chunk of K takes 5.9 us per round of 256 tiles, 6.3
+// where many rounds fill the chip, and 6.7e5 results are written per us.
+double gemm_us(int M, int N, int K) {
+    const double tiles = (double)((M + GT - 1) / GT) * ((N + GT - 1) / GT), rounds = ceil(tiles / 256.0);
+    return 2.0 + (K + GK - 1) / GK * fmax(5.9 * rounds, 6.3 * tiles / 256.0) + (double)M * N / 6.7e5;
+}
+
+// The route of a field: the products cost in proportion to the truncation, the transforms hardly less for a small one (us, products
+// and fast: m = 1000, 8 x 8 47 and 100, 128 x 128 135 and 101; m = 4095, 32 x 32 202 and 1135, 1024 x 1024 3010 and 1330;
+// m = 4096, 32 x 32 172 and 213, 128 x 128 437 and 312).  By the time of all three outputs, also where fewer are asked for: an
+// output's bits do not depend on the others'.
+bool field_by_fft(const BinFft &f, int Mu, int Mp) {
+    return f.L > 0 && bin_fft_field_us(f, Mu) < 3.0 + 2 * gemm_us(Mu, f.m, Mp) + 3 * gemm_us(f.m, f.m, Mu);
+}
+
 BinOp dense(const double *p, int ld) { return BinOp{p, ld, 0, 0, 0.0}; }
 BinOp trig(int kind, bool freq_is_row, double wscale) { return BinOp{nullptr, 0, kind, freq_is_row ? 1 : 0, wscale}; }
 
@@ -445,8 +460,8 @@ int pp_bin_coeffs(const pp_bin_problem *B, const double *P, double *a, void *ws,
     double *tab = (double *)((char *)ws + L.tab), *Q = (double *)((char *)ws + L.tmp);
     const int m = B->m;
     TimedLaunch t("bin_coeffs", s);
-    // as FFTs wherever a workgroup can hold one, as matrix products elsewhere
-    if (const BinFft f = bin_fft_plan(m); f.L > 0) {
+    // as FFTs where a workgroup can hold one and they are faster, as matrix products elsewhere
+    if (const BinFft f = bin_fft_plan(m); bin_fft_for_coeffs(f, B->Mu, B->Mp)) {
         if (launch_bin_fft_tables(f, tab, s) != hipSuccess ||
             launch_bin_fft_coeffs(f, tab, P, Q, a, B->Mu, B->Mp, B->W, B->H, s) != hipSuccess)
             return PP_ERR_DEVICE;
@@ -477,8 +492,8 @@ int pp_bin_field(const pp_bin_problem *B, const double *a, double *psi, double *
     double *R = (double *)((char *)ws + L.tmp), *Rs = R + (size_t)Mu * m;
     const double wu = kPi / B->W, vp = kPi / B->H;
     TimedLaunch t("bin_field", s);
-    // as FFTs wherever a workgroup can hold one, as matrix products elsewhere
-    if (const BinFft f = bin_fft_plan(m); f.L > 0) {
+    // as FFTs where a workgroup can hold one and they are faster, as matrix products elsewhere
+    if (const BinFft f = bin_fft_plan(m); field_by_fft(f, Mu, Mp)) {
         if (launch_bin_fft_tables(f, tab, s) != hipSuccess ||
             launch_bin_fft_field(f, tab, a, R, Rs, psi, xix, xiy, Mu, Mp, B->W, B->H, s) != hipSuccess)
             return PP_ERR_DEVICE;

@@ -412,15 +412,12 @@ hipError_t launch_pass(const BinFft &f, const FftArgs &A, int jobs, hipStream_t 
     return hipGetLastError();
 }
 
-// Points per workgroup: row passes 2048 (36 KB of LDS: four workgroups per CU) or one transform; column passes four
-// transforms, eight columns, so that a row of them fills half a cache line, up to 8192 points.  `count`: rows or columns.
+// `count`: rows or columns.
 template <int PASS>
 hipError_t launch_points(const BinFft &f, FftArgs A, int count, int jobs, hipStream_t s) {
     constexpr bool COL = PASS == COL_FWD || PASS == COL_INV;
-    int pts = COL ? 4 * f.L : f.L;
-    pts = pts < 2048 ? 2048 : pts > 8192 ? 8192 : pts;
-    const int G = pts / f.L;
-    A.groups = ((count + 1) / 2 + G - 1) / G;
+    const int pts = bin_fft_points(f, COL);
+    A.groups = bin_fft_workgroups(f, COL, count);
     if (pts == 2048) return launch_pass<2048, PASS>(f, A, jobs, s);
     if (pts == 4096) return launch_pass<4096, PASS>(f, A, jobs, s);
     return launch_pass<8192, PASS>(f, A, jobs, s);
