@@ -42,9 +42,9 @@ __global__ __launch_bounds__(64) void k_reduce_scale(const T *__restrict__ part,
     // A split's plane may begin at any element.
     typedef T Vec __attribute__((ext_vector_type(4), aligned(sizeof(T))));
     const size_t MM = (size_t)Mu * (size_t)Mp;
-    const size_t idx = (size_t)blockIdx.x * kRedCoefs + 4 * threadIdx.x;
-    // where fewer than four coefficients are left, the plane's last four
-    const size_t at = MM < 4 ? 0 : min(idx, MM - 4);
+    // four coefficients a lane: where fewer are left, the plane's last four; of a plane of fewer, one a lane
+    const size_t idx = MM < 4 ? threadIdx.x : (size_t)blockIdx.x * kRedCoefs + 4 * threadIdx.x;
+    const size_t at = MM < 4 ? idx : min(idx, MM - 4), end = MM < 4 ? min(idx + 1, MM) : MM;
     double At[4] = {};
     if (MM >= 4) {
         const T *__restrict__ p = part + at;
@@ -64,15 +64,15 @@ __global__ __launch_bounds__(64) void k_reduce_scale(const T *__restrict__ part,
             if (s + k < splits)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) At[c] += (double)v[k][c];
-    } else {
-        for (int s = 0; s < splits; ++s)
-            for (int c = 0; c < (int)MM; ++c) At[c] += (double)part[(size_t)s * MM + c];
+    } else if (at < MM) {
+#pragma unroll 16
+        for (int s = 0; s < splits; ++s) At[0] += (double)part[(size_t)s * MM + at];
     }
     double e = 0.0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const size_t id = at + c;
-        if (id < idx || id >= MM) continue;   // another lane's, or none
+        if (id < idx || id >= end) continue;   // another lane's, or none
         const int u = (int)(id / (size_t)Mp), q = (int)(id % (size_t)Mp);
         const double wu = (double)u * kPi / W, vp = (double)q * kPi / H;
         const double wt = u ? wu : 1.0, vt = q ? vp : 1.0;
