@@ -88,20 +88,23 @@ __global__ __launch_bounds__(64) void k_reduce_scale(const T *__restrict__ part,
     if (threadIdx.x == 0) epart[blockIdx.x] = e;
 }
 
+// One workgroup of as many waves as there are partials for, at most kEnergyThreads (an energy of 5 blocks: 7.8 us with 64
+// threads, 8.5 with 1024; the waves without partials only waited for each other).
 constexpr int kEnergyThreads = 1024;
 
 __global__ __launch_bounds__(kEnergyThreads) void k_energy_final(const double *__restrict__ epart, int nb,
                                                                  double *__restrict__ E) {
     __shared__ double scratch[kEnergyThreads / 64];
     double v = 0.0;
+    const int threads = blockDim.x;
     int k = threadIdx.x;
-    for (; k + 3 * kEnergyThreads < nb; k += 4 * kEnergyThreads) {
+    for (; k + 3 * threads < nb; k += 4 * threads) {
         double x[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = epart[k + r * kEnergyThreads];
+        for (int r = 0; r < 4; ++r) x[r] = epart[k + r * threads];
         v += (x[0] + x[1]) + (x[2] + x[3]);
     }
-    for (; k < nb; k += kEnergyThreads) v += epart[k];
+    for (; k < nb; k += threads) v += epart[k];
     const double s = block_sum(v, scratch);
     if (threadIdx.x == 0) *E = 0.5 * s;
 }
@@ -167,7 +170,8 @@ hipError_t launch_reduce_scale(const void *part, bool part_f32, int splits, int 
 }
 
 hipError_t launch_energy_final(const double *epart, int nblocks, double *E, hipStream_t s) {
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kEnergyThreads), 0, s, epart, nblocks, E);
+    const int threads = nblocks < kEnergyThreads ? (nblocks + 63) / 64 * 64 : kEnergyThreads;
+    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(threads), 0, s, epart, nblocks, E);
     return hipGetLastError();
 }
 
