@@ -506,10 +506,14 @@ hipError_t launch_fwd_mat(const FwdPlan &pl, int64_t n, int Mu, int Mp, double W
     if (pl.tu == 64) return launch(k_fwd_mat<T, 64>, pl.tiles_p);
     if (pl.tu != 128) return hipErrorInvalidValue;
     if constexpr (sizeof(T) == 4) {
-        // FP32: four tiles as one of 256 x 256 (twice the MFMAs per generated value) where no column or row is padded for it
-        // and every CU still gets two of them; the plan's splits stay, so that the sums of a split do not change
+        // FP32: four tiles as one of 256 x 256 (twice the MFMAs per generated value, one workgroup per CU) where no column or row is
+        // padded for it, a split is long enough for the larger prologue and stores, and the rounds of 256 workgroups are
+        // nearly full; the plan's splits stay, so that the sums of a split do not change.  (128 and 256, us: 512 x 512, 13
+        // chunks a split 284 and 283, 49 chunks 958 and 933; 1024 x 1024, 5 chunks 139 and 149; 3000 x 3000, 2.25 rounds, 40 chunks
+        // 883 and 1095.)
         const int tu = (pl.tiles_u + 1) / 2, tp = (pl.tiles_p + 1) / 2;
-        if (pl.tiles_u % 2 == 0 && pl.tiles_p % 2 == 0 && (int64_t)tu * tp * pl.splits >= 512) {
+        const int64_t wgs = (int64_t)tu * tp * pl.splits, rounds = (wgs + 255) / 256;
+        if (pl.tiles_u % 2 == 0 && pl.tiles_p % 2 == 0 && pl.chunks_per_split >= 12 && wgs >= 480 && 100 * wgs >= 93 * 256 * rounds) {
             grid.x = tu * tp;
             return launch(k_fwd_mat<T, 256>, tp);
         }
