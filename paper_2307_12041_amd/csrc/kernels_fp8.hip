@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) void k_fwd_fp8(int64_t n, int Mu, int Mp, cons
     const int64_t rows = phase_rows(n);
     int tile;
     int64_t split;
-    fwd_tile_split(tile, split);
+    fwd_tile_split(tile, split, true);
     const int tu0 = (tile / tiles_p) * 256, tp0 = (tile % tiles_p) * 256;
     const int wu = 128 * (wave >> 1), wp = 128 * (wave & 1);
     const int64_t c_begin = split * chunks_per_split;
