@@ -49,7 +49,8 @@ struct RowOut {
 
 // The contractions of one launch: the second one's N tiles follow the first one's on grid axis y (tiles0 of them; a launch
 // of one contraction has no workgroup beyond).  Each alone fills the chip badly where its workgroups are few, and its last
-// wave of workgroups leaves CUs idle.  The one with the longer K loop is the first: begun last, its few long workgroups would run
+// wave of workgroups leaves CUs idle.  Where one has a K loop of more than twice the chunks it is the first: begun last, its few long
+// workgroups would run
 // on, two to a CU, while other CUs are idle (gradients of unequal axes: FP64, 20,000 blocks, 4096 x 64 1241 us so,
 // 958 as two launches, 667 with the longer first; bf16mix, 53,629 blocks, 1175 x 33 153, 140, 128).
 template <typename A> struct AxisPair {

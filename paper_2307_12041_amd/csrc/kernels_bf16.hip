@@ -1753,7 +1753,7 @@ __global__ __launch_bounds__(256) void k_bwd1_bf16(int64_t n, AxisPair<BwdAxisBf
     unsigned t = blockIdx.y, b = blockIdx.x;
     if (nb1 != 0 && nb2 != 0) {
         unsigned w = blockIdx.y * gridDim.x + blockIdx.x, tiles = gridDim.y, t0 = 0;
-        if (P.a[0].Ka > 2 * P.a[1].Ka) {
+        if (P.a[0].Kh > 2 * P.a[1].Kh) {
             const unsigned own = gridDim.x * (unsigned)P.tiles0;
             if (w < own) tiles = (unsigned)P.tiles0;
             else w -= own, tiles -= (unsigned)P.tiles0, t0 = (unsigned)P.tiles0;
@@ -2030,7 +2030,7 @@ namespace {
 template <int KA, int E1, int E2>
 hipError_t launch_rowform_bf16(bool x3, int64_t n, const BwdAxisBf16 &ax0, const BwdAxisBf16 *ax1, hipStream_t s) {
     AxisPair<BwdAxisBf16> P{{ax0, ax1 ? *ax1 : ax0}, 0};
-    if (ax1 && ax1->Ka > ax0.Ka) std::swap(P.a[0], P.a[1]);   // (see AxisPair)
+    if (ax1 && ax1->Kh > 2 * ax0.Kh) std::swap(P.a[0], P.a[1]);   // (see AxisPair)
     int tiles[2] = {0, 0};
     for (int k = 0; k < (ax1 ? 2 : 1); ++k) {
         const BwdAxisBf16 &ax = P.a[k];

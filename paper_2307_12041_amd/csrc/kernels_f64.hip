@@ -533,7 +533,8 @@ hipError_t launch_rowform_tile(int64_t n, const BwdAxis &ax0, const BwdAxis *ax1
 
 template <typename T, int KA_KIND, int EP1, int EP2>
 hipError_t launch_rowform(const BwdPlan &pl, int64_t n, const BwdAxis &ax0, const BwdAxis *ax1, hipStream_t s) {
-    if (ax1 && ax1->Ka > ax0.Ka) return launch_rowform<T, KA_KIND, EP1, EP2>(pl, n, *ax1, &ax0, s);   // (see AxisPair)
+    if (ax1 && (ax1->Ka + kK - 1) / kK > 2 * ((ax0.Ka + kK - 1) / kK))
+        return launch_rowform<T, KA_KIND, EP1, EP2>(pl, n, *ax1, &ax0, s);   // (see AxisPair)
     if (!(pl.tb == 128 && pl.kk == kK && (pl.tn == 128 || (pl.tn == 256 && sizeof(T) == 4)))) return hipErrorInvalidValue;
     if (n == 0) return hipSuccess;
     if ((ax0.out.r && ax0.Nb > pl.tn) || (ax1 && ax1->out.r && ax1->Nb > pl.tn)) return hipErrorInvalidValue;
