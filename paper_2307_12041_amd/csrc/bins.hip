@@ -7,9 +7,9 @@
 //     a'_up = sum_l C_u(l) sum_j P_lj C_p(j),                        a_up = disa factor(u,p) a'_up,
 //     psi_lj = sum_u C_u(l) R_uj,   R_uj = sum_p a_up C_p(j),
 //     xi_x,lj = sum_u (u pi/W) S_u(l) R_uj,   xi_y,lj = sum_u C_u(l) Rs_uj,  Rs_uj = sum_p a_up (p pi/H) S_p(j).
-// Each is one FP64 MFMA GEMM whose trigonometric operand is read from a table of cos and sin of
-// k pi / (2m), k in [0, 4m), indexed by f (2s+1) mod 4m (exact integer reduction, so every entry
-// carries only the table's one rounding).
+// They are fast transforms (bins_fft.hip) where those are faster.  Elsewhere each is one FP64 MFMA GEMM whose
+// trigonometric operand is read from a table of cos and sin of k pi / (2m), k in [0, 4m), indexed by f (2s+1) mod 4m (exact
+// integer reduction, so every entry carries only the table's one rounding).
 #include <math.h>
 
 #include "bins_fft.h"
@@ -227,16 +227,6 @@ __device__ __forceinline__ void binop_issue(const BinOp &o, const double *__rest
     }
 }
 
-// Epilogue factor of the binned coefficients (eqs. disa-a..d) for row u, column p.
-__device__ __forceinline__ double disa_factor(int u, int p, double W, double H, int m) {
-    const double pi = kPi;
-    if (u == 0 && p == 0) return 0.0;
-    if (u == 0) return 4.0 * H * H / ((double)p * p * p * pi * pi * pi * m) * sinpi(p / (2.0 * m));
-    if (p == 0) return 4.0 * W * W / ((double)u * u * u * pi * pi * pi * m) * sinpi(u / (2.0 * m));
-    return 16.0 * W * W * H * H / ((double)u * p * ((double)u * u * H * H + (double)p * p * W * W) * pi * pi * pi * pi) *
-           sinpi(u / (2.0 * m)) * sinpi(p / (2.0 * m));
-}
-
 // 128 x 128 output tile per workgroup of 8 waves (2 x 4 sub-tiles of 64 x 32, eight 16 x 16
 // accumulators each); K chunks of 32 in LDS, A as [i][k] with rows of KP = 34 doubles and B as
 // [k][j] with rows of JP = 144 doubles.  With 64 banks of 4 bytes, the MFMA operand reads (16
@@ -322,7 +312,7 @@ __global__ __launch_bounds__(GTHREADS) void k_bin_gemm(int M, int N, int K, BinO
                 const int col = c0 + wc + 16 * b + (lane & 15);
                 if (row < M && col < N) {
                     double v = acc[a][b][r];
-                    if (DISA) v *= disa_factor(row, col, W, H, m);
+                    if (DISA) v *= disa_factor(row, col, sinpi(row / (2.0 * m)), sinpi(col / (2.0 * m)), W, H, m);
                     C[(size_t)row * ldc + col] = v;
                 }
             }

@@ -3,7 +3,19 @@
 
 #include <hip/hip_runtime.h>
 
+#include "common.h"
+
 namespace pp {
+
+// Epilogue factor of the binned coefficients (eqs. disa-a..d) for row u, column p; su = sin(u pi / 2m), sp likewise.
+__device__ __forceinline__ double disa_factor(int u, int p, double su, double sp, double W, double H, int m) {
+    const double pi = kPi;
+    if (u == 0 && p == 0) return 0.0;
+    if (u == 0) return 4.0 * H * H / ((double)p * p * p * pi * pi * pi * m) * sp;
+    if (p == 0) return 4.0 * W * W / ((double)u * u * u * pi * pi * pi * m) * su;
+    return 16.0 * W * W * H * H / ((double)u * p * ((double)u * u * H * H + (double)p * p * W * W) * pi * pi * pi * pi) *
+           su * sp;
+}
 
 // Transform length m (bins per axis) as complex transforms of length L, a power of two:
 //   m itself a power of two in [64, 8192]: L = m;

@@ -198,16 +198,6 @@ __global__ __launch_bounds__(1024) void k_fft_tables_chirp(int N, int lg, cplx *
     }
 }
 
-// Epilogue factor of the binned coefficients (eqs. disa-a..d) for row u, column p; su = sin(u pi / 2m), sp likewise.
-__device__ __forceinline__ double disa_factor(int u, int p, double su, double sp, double W, double H, int m) {
-    const double pi = kPi;
-    if (u == 0 && p == 0) return 0.0;
-    if (u == 0) return 4.0 * H * H / ((double)p * p * p * pi * pi * pi * m) * sp;
-    if (p == 0) return 4.0 * W * W / ((double)u * u * u * pi * pi * pi * m) * su;
-    return 16.0 * W * W * H * H / ((double)u * p * ((double)u * u * H * H + (double)p * p * W * W) * pi * pi * pi * pi) *
-           su * sp;
-}
-
 enum Pass { ROW_FWD, COL_FWD, ROW_INV, COL_INV };
 
 // One transform of a pass: input and output arrays, and for inverse passes cosine or sine of k scale c_k.

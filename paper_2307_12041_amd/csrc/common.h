@@ -50,9 +50,8 @@ struct RowOut {
 // The contractions of one launch: the second one's N tiles follow the first one's on grid axis y (tiles0 of them; a launch
 // of one contraction has no workgroup beyond).  Each alone fills the chip badly where its workgroups are few, and its last
 // wave of workgroups leaves CUs idle.  Where one has a K loop of more than twice the chunks it is the first: begun last, its few long
-// workgroups would run
-// on, two to a CU, while other CUs are idle (gradients of unequal axes: FP64, 20,000 blocks, 4096 x 64 1241 us so,
-// 958 as two launches, 667 with the longer first; bf16mix, 53,629 blocks, 1175 x 33 153, 140, 128).
+// workgroups would run on, two to a CU, while other CUs are idle (gradients of unequal axes: FP64, 20,000 blocks, 4096 x 64
+// 1241 us so, 958 as two launches, 667 with the longer first; bf16mix, 53,629 blocks, 1175 x 33 153, 140, 128).
 template <typename A> struct AxisPair {
     A a[2];
     int tiles0;
@@ -244,10 +243,11 @@ hipError_t launch_setup_bf16(int64_t n, const AxisTables &x, const AxisTables &y
                              int Mp, double W, double H, const PrepBf16 (&prep)[2], hipStream_t s);
 hipError_t launch_fwd_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                            const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
-// Mixed split: the rx x ry low-frequency tiles with k_fwd1_bf16 (three products), the others with
-// the one-product kernel; same partials and plan as launch_fwd_bf16.
+// The splits added on the way: pl.groups FP64 planes instead of pl.splits FP32 ones.
 hipError_t launch_fwd_sum_bf16(const FwdPlan &pl, bool x3, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                                const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, double *part, hipStream_t s);
+// Mixed split: the rx x ry low-frequency tiles with k_fwd1_bf16 (three products), the others with
+// the one-product kernel; same partials and plan as launch_fwd_bf16.
 hipError_t launch_fwd_bf16_mix(const FwdPlan &pl, int rx, int ry, int64_t n, int Mu, int Mp, const PhaseRec *tx,
                                const PhaseRec *ty, const RunSeed *sx, const RunSeed *sy, float *part, hipStream_t s);
 size_t bwd_bf16_operand_elems(int Np, int Kh);   // bf16 elements of one tiled backward operand
