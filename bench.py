@@ -317,16 +317,20 @@ def main():
     log(f"[bench] {args.precision}: {dt / args.steps * 1e3:.2f} ms/step, {value:.4e} pairs/s; stages "
         + ", ".join(f"{k}={v[0] / v[1]:.2f}ms x{v[1] // args.steps}" for k, v in stages.items()))
 
-    # Roofline of the dominant kernel: the stage with the largest total time.
+    # Roofline of the dominant kernel: the stage with the largest total time.  gx and gy are two records of one launch, except
+    # for the FP8 types and the stored basis, which launch each.
     dom = max(("fwd", "bwd"), key=lambda s: stages[s][0])
-    avg_ms = stages[dom][0] / stages[dom][1]
-    alg_flops = 2.0 * pairs                  # one contraction: 2 flops per (block, u, p)
+    per_step = stages[dom][1] // args.steps                    # contractions
+    joint = dom == "bwd" and args.precision not in ("fp8x3", "fp8") and args.basis == "recompute"
+    launches = 1 if joint else per_step
+    avg_ms = stages[dom][0] / (args.steps * launches)
+    alg_flops = 2.0 * pairs * per_step / launches              # one contraction: 2 flops per (block, u, p)
     achieved = alg_flops / (avg_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.precision]
     X = "x3" if args.precision == "bf16x3" else "plain"
     if args.basis == "recompute":
         kernel_name = {"fwd": f"k_fwd1_bf16<{X}> (coefficient contraction)",
-                       "bwd": f"k_bwd1_bf16<{X}> (gradient contraction, gx and gy launches)"}[dom]
+                       "bwd": f"k_bwd1_bf16<{X}> (gradient contractions, gx and gy in one launch)"}[dom]
     else:
         kernel_name = {"fwd": f"k_fwd_bf16_st<{X}> (coefficient contraction)",
                        "bwd": f"k_bwd_bf16_st<{X}> (gradient contraction, gx and gy launches)"}[dom]
@@ -339,7 +343,7 @@ def main():
                        "bwd": f"k_bwd_fp8<{X}> (gradient contraction, gx and gy launches)"}[dom]
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4), "traffic": measured_traffic(wl.name, args.precision, dom),
-                "kernel": kernel_name, "avg_launch_ms": round(avg_ms, 3), "launches_per_step": stages[dom][1] // args.steps,
+                "kernel": kernel_name, "avg_launch_ms": round(avg_ms, 3), "launches_per_step": launches,
                 "algorithmic_flops_per_launch": alg_flops,
                 "executed_mfma_tflops": round(achieved * MFMA_MULT[args.precision], 2),
                 "executed_mfma_frac": round(achieved * MFMA_MULT[args.precision] / peak, 4),
@@ -480,8 +484,6 @@ def main():
         tf, _ = pp.timing_query("bin_field")
         ti, _ = pp.timing_query("bin_interp")
         pp.timing_enable(False)
-        gemm_flops = 2.0 * m_bins * Mb * m_bins + 2.0 * Mb * Mb * m_bins + 2 * 2.0 * Mb * m_bins * Mb \
-            + 3 * 2.0 * m_bins * m_bins * Mb
         if ref is not None:
             a_dir, g_dir, dir_name = ref[1], (ref[2], ref[3]), "fp64 direct sum (GPU)"
         else:
@@ -494,9 +496,8 @@ def main():
         gdir = np.concatenate([g_dir[0].cpu().numpy(), g_dir[1].cpu().numpy()])
         bins = {"m": m_bins, "M": Mb, "density_ms": td, "coeffs_ms": tcf, "field_ms": tf, "interp_ms": ti,
                 "total_ms": td + tcf + tf + ti,
-                "transforms": "dense FP64 GEMMs against cos/sin tables (O(m^3) per transform), not the FFT of "
-                              "Sec. III-D; the cost is that of this comparison path",
-                "transform_gemm_tflops_fp64": round(gemm_flops / ((tcf + tf) * 1e-3) / 1e12, 2),
+                "transforms": "FP64 fast cosine and sine transforms (FFTs in LDS); FP64 matrix products where few "
+                              "frequencies of many bins make them faster",
                 "compared_with": dir_name,
                 "coeffs_rel_diff": rel(abn, adn),
                 f"coeffs_rel_diff_u_p_below_{lo}": rel(abn[:lo, :lo], adn[:lo, :lo]),
